@@ -229,22 +229,23 @@ int aes_cbc_encrypt_msgs_variant(const uint32_t *rk, int nr, const aes_cbc_msg *
 /*
  * aes_cbc_decrypt_msgs -- CBC decryption (section 3.1.2, eq 2 read as above:
  * P_i = invcipher(C_i) XOR C_{i-1}, C_0 = iv) of the same kind of message
- * set, under one key, in one launch: one message per lane, its blocks
- * independent of each other, each XORed with the preceding ciphertext block.
+ * set, under one key, in one launch; every block is independent of the
+ * others, XORed with the preceding ciphertext block.
  *   rk:       host pointer to the DECRYPTION schedule (rk_dec), copied.
  *   Other arguments, checks, skipped messages and errors as for
  *   aes_cbc_encrypt_msgs; a message may run in place (equal ranges in one
  *   arena).  For one long message aes_cbc_decrypt is the faster call (every
  *   block of it in parallel); this call is for many messages at once.
- * Two kernels: one message per lane (bpt = blocks a lane decrypts at once:
- * 1, 2 or 4), for short messages, or one wave per message (bpt =
- * AES_BPT_WAVE_MSG + 1 or 2 blocks per lane per 64-block unit, every
- * access of the wave contiguous), for messages of 64 blocks or more.  The
- * _variant form takes that bpt, wg, a table placement (not bitsliced) and
- * grid.  The default uses 4 tables, one wave per message with 2 blocks per
- * lane when the input arena averages at least 64 blocks per message (one
- * lane per message with 4 otherwise), and the smallest workgroup (up to 1024
- * threads) that gives every compute unit the same number of waves.
+ * The default walks the set block by block, 64 blocks of consecutive
+ * messages per wave at a time, so that lengths may vary freely; between
+ * separate arenas several waves share the messages, so a few long ones also
+ * fill the device.  In one arena no message is split over waves.
+ * The _variant form runs one of two other kernels: one message per lane (bpt
+ * = blocks a lane decrypts at once: 1, 2 or 4), or one wave per message
+ * (bpt = AES_BPT_WAVE_MSG + 1 or 2 blocks per lane per 64-block unit), with
+ * the given wg, table placement (not bitsliced) and grid.  The default takes
+ * the first for 2^17 messages or more of at most 4 blocks on average (on 256
+ * CUs) and the second within one arena for messages of 64 blocks or more.
  * Asynchronous on stream.
  */
 int aes_cbc_decrypt_msgs(const uint32_t *rk, int nr, const aes_cbc_msg *msgs_dev, size_t nmsgs, const void *in_base,

@@ -292,18 +292,26 @@ aes_variant cbc_msgs_default(size_t nmsgs, int cus)
     return aes_variant{quads ? AES_BPT_COLUMN : 8, wg, AES_PLACEMENT_TTABLE4, 0};
 }
 
-// Shape of aes_cbc_decrypt_msgs when the caller names none, on 4 tables: one
-// wave per message (2 blocks per lane per unit) when the input arena averages
-// at least 64 blocks per message, so that a wave's lanes all have blocks,
-// else one message per lane with 4 independent blocks at a time; workgroups
-// just large enough to give every CU the same number of waves, up to 1024.
-aes_variant cbc_dec_msgs_default(size_t nmsgs, size_t in_blocks, int cus)
+// Shape of aes_cbc_decrypt_msgs when the caller names none.  The kernel that
+// walks the set block by block (kCbcFlat, which splits the work itself) takes
+// all but two kinds of set (AES-128, other kernel -> this one):
+//   - many very short messages, at most 4 blocks of the arena each and half a
+//     wave of them or more for every wave the device holds: finding each
+//     block's message costs more than lanes idle at ragged ends (2^20
+//     messages of 4 blocks 60 -> 71 us, of 8 blocks 146 -> 135), so one
+//     message per lane with 4 blocks at a time;
+//   - messages that fill a wave (64 blocks of the arena each) within one
+//     arena, where no message may be split over waves: one wave per message
+//     has less to do (4096 of up to 16 KiB 43 -> 44 us).
+// Those two take workgroups just large enough to give every CU as many waves.
+aes_variant cbc_dec_msgs_default(size_t nmsgs, size_t in_blocks, bool one_arena, int cus)
 {
-    const uint64_t c = cus > 0 ? (uint64_t)cus : 256u;
-    const bool wave = nmsgs > 0 && in_blocks / nmsgs >= 64u;
+    const uint64_t c = cus > 0 ? (uint64_t)cus : 256u, mean = in_blocks / nmsgs;
+    const bool lanes = mean <= 4u && nmsgs >= 32u * 16u * c, wave = one_arena && mean >= 64u;
+    if (!lanes && !wave)
+        return aes_variant{kCbcFlat, 0, AES_PLACEMENT_TTABLE4, 0};
     const uint64_t waves = wave ? nmsgs : (nmsgs + 63u) / 64u;
-    const uint64_t per_cu = (waves + c - 1) / c;
-    const int wg = (int)std::min<uint64_t>(1024u, 64u * std::max<uint64_t>(per_cu, 1u));
+    const int wg = (int)std::min<uint64_t>(1024u, 64u * ((waves + c - 1) / c));
     return aes_variant{wave ? AES_BPT_WAVE_MSG + 2 : 4, wg, AES_PLACEMENT_TTABLE4, 0};
 }
 
@@ -356,7 +364,9 @@ int run_cbc_msgs(bool decrypt, const uint32_t* rk, int nr, const aes_cbc_msg* ms
     if (cus <= 0)
         return fail(AES_EHIP, "cannot query the current HIP device");
     const aes_variant chosen =
-        v != nullptr ? *v : decrypt ? cbc_dec_msgs_default(nmsgs, in_blocks, cus) : cbc_msgs_default(nmsgs, cus);
+        v != nullptr ? *v
+        : decrypt    ? cbc_dec_msgs_default(nmsgs, in_blocks, in_base == out_base, cus)
+                     : cbc_msgs_default(nmsgs, cus);
     v = &chosen;
     LaunchShape shape{v->bpt, v->wg, v->grid};
     hipError_t e =

@@ -24,4 +24,12 @@ hipError_t launch_cbc_decrypt_msgs(const LaunchShape& shape, int placement, int 
                                    const void* in, uint64_t in_blocks, void* out, uint64_t out_blocks,
                                    uint32_t* rejected, const RoundKeys& rk, int cus, hipStream_t stream);
 
+// Decryption walked block by block whatever the lengths (aes_cbc_dec_flat.hip):
+// launch_cbc_decrypt_msgs with shape.bpt = kCbcFlat, which picks its own
+// workgroup size, grid and split.
+constexpr int kCbcFlat = -1;
+hipError_t launch_cbc_dec_flat(int nr, const void* msgs, uint64_t nmsgs, const void* in, uint64_t in_blocks,
+                               void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, int cus,
+                               hipStream_t stream);
+
 }  // namespace aesgpu

@@ -364,3 +364,61 @@ def test_one_gib_of_four_kib_messages_on_samples(oracle_lib):
         s = to_host(src[a:a + blocks * 16])
         want = oracle_lib.cbc_encrypt(key, recs[m]["iv"].tobytes(), s)
         assert first_mismatch(to_host(out[a:a + blocks * 16]), want) is None, int(m)
+
+
+# lengths (drawn by the name's rule), messages, arena blocks per message, one arena for both
+FLAT_SETS = {
+    "one_block": (lambda g, n: np.ones(n), 1, 1, False),
+    "around_a_step": (lambda g, n: np.array([63, 64, 65, 1, 127, 128, 129, 0, 0, 2])[:n], 10, 130, False),
+    "long_few": (lambda g, n: np.array([9000, 0, 4097]), 3, 9001, False),
+    "one_wave_group": (lambda g, n: g.integers(0, 200, n), 64, 200, False),
+    "group_and_one": (lambda g, n: g.integers(0, 40, n), 65, 40, False),
+    "sparse": (lambda g, n: (g.random(n) < 0.02) * g.integers(1, 90, n), 9000, 90, False),
+    "shared_groups": (lambda g, n: g.integers(0, 5, n), 50000, 6, False),
+    "several_rounds": (lambda g, n: (g.random(n) < 0.3) * 1, 270011, 5, False),
+    "lanes": (lambda g, n: g.integers(0, 3, n), 140003, 3, False),
+    "in_place_short": (lambda g, n: g.integers(0, 60, n), 3000, 62, True),
+    "in_place_long": (lambda g, n: g.integers(0, 300, n), 300, 300, True),
+}
+
+
+@pytest.mark.parametrize("name", FLAT_SETS)
+def test_decrypt_default_over_set_shapes(oracle_lib, name):
+    """The default decryption over sets whose lengths, counts and arenas take
+    every split of the work (a wave's group, groups shared by waves, rounds of
+    groups, one message per lane or wave), with refused records between."""
+    torch = cuda()
+    lengths, n, room, one_arena = FLAT_SETS[name]
+    g = inputs.rng(11, n)
+    keybits = (128, 192, 256)[n % 3]
+    key = inputs.random_key(870 + n, keybits)
+    ks = aes.aes_expand_key(key)
+    recs = np.zeros(n, dtype=aes.CBC_MSG_DTYPE)
+    nb = np.asarray(lengths(g, n)).astype(np.int64)
+    assert nb.max() <= room
+    recs["nblocks"] = nb
+    recs["in_block"] = np.arange(n) * room + g.integers(0, room - nb + 1)
+    recs["out_block"] = recs["in_block"] if one_arena else g.permutation(n) * room
+    recs["iv"] = g.integers(0, 256, (n, 16))
+    bad = np.zeros(n, dtype=bool)
+    if n > 10:  # refused: a reserved field, a range that leaves its arena
+        bad[1::97] = bad[5::1001] = True
+        recs["reserved"][1::97] = 1
+        recs["in_block"][5::1001] = n * room
+        recs["nblocks"][5::1001] = 1
+    good = np.nonzero(~bad & (nb > 0))[0]
+    src = inputs.random_bytes(871 + n, 16 * n * room).reshape(-1, 16)
+    # every block of the good messages: its message, its place in it
+    msg = np.repeat(good, nb[good])
+    k = np.arange(msg.size) - np.repeat(np.cumsum(nb[good]) - nb[good], nb[good])
+    at = recs["in_block"][msg].astype(np.int64) + k
+    prev = np.where((k == 0)[:, None], recs["iv"][msg], src[at - 1])
+    plain = oracle_lib.ecb_decrypt(key, np.ascontiguousarray(src[at]).reshape(-1)).reshape(-1, 16) ^ prev
+    src_dev = to_dev(src.reshape(-1))
+    out = src_dev if one_arena else torch.full((16 * n * room,), SENTINEL, dtype=torch.uint8, device="cuda")
+    want = src.copy() if one_arena else np.full_like(src, SENTINEL)
+    want[recs["out_block"][msg].astype(np.int64) + k] = plain
+    rej = torch.zeros(1, dtype=torch.int32, device="cuda")
+    run_dec(ks, recs, src_dev, out, rejected=rej)
+    assert int(rej.item()) == bad.sum()
+    assert first_mismatch(to_host(out), want.reshape(-1)) is None
