@@ -199,7 +199,7 @@ int aes_cbc_decrypt_variant(const uint32_t *rk, int nr, const uint8_t *iv, const
  * One chain has one block in flight, so a launch keeps every compute unit
  * busy only with about 2^17 messages or more; fewer are bound by the latency
  * of a block's rounds.  The consecutive entries that one wave walks (64, or
- * 16 for short lists) take as long as the longest of them: list messages of
+ * 16 or 4 for short lists) take as long as the longest of them: list messages of
  * similar length together.
  * Asynchronous on stream.
  */
@@ -221,7 +221,8 @@ int aes_cbc_encrypt_msgs(const uint32_t *rk, int nr, const aes_cbc_msg *msgs_dev
  * placement, bpt 8 when there are at least 8 one-lane waves per compute unit
  * (2^17 messages on 256 CUs) and AES_BPT_COLUMN below that, and the smallest
  * workgroup (up to 1024 threads) that gives every compute unit the same
- * number of waves. */
+ * number of waves; up to 72 messages per compute unit it takes a kernel of
+ * its own with sixteen lanes per message, one lookup per lane per round. */
 int aes_cbc_encrypt_msgs_variant(const uint32_t *rk, int nr, const aes_cbc_msg *msgs_dev, size_t nmsgs,
                                  const void *in_base, size_t in_blocks, void *out_base, size_t out_blocks,
                                  uint32_t *rejected_dev, const aes_variant *variant, void *stream);

@@ -274,17 +274,26 @@ int run_cbc_decrypt(const uint32_t* rk, int nr, const uint8_t* iv, const void* i
     return AES_OK;
 }
 
-// Shape of aes_cbc_encrypt_msgs when the caller names none, on the 4-table
-// placement (one workgroup per CU).  With at least 8 one-lane-per-message
-// waves per CU (64 messages each) the lanes walk whole states, 8 blocks (one
-// 128-byte line) per load and store; with fewer, a block's rounds are the
-// bound and four lanes share a message (AES_BPT_COLUMN, 16 messages per
-// wave), which shortens them.  Workgroups are just large enough to give
-// every CU the same number of waves, up to 1024 threads, so a short list
-// still spreads over all CUs instead of filling a few.
+// Shape of aes_cbc_encrypt_msgs when the caller names none: as many lanes per
+// message as the list leaves idle, for the more lanes, the shorter a round
+// (AES-128, 4 KiB messages, ns per round of a lone chain 42 with sixteen lanes,
+// 55 with four).
+//   - up to 72 messages per CU (18 waves of 4): sixteen lanes per message
+//     (kCbcRow; 16384 messages 164 -> 137 us against four lanes, 18000
+//     AES-256 218 -> 193, but 24576 162 -> 168);
+//   - below 8 one-lane waves per CU (2^17 messages on 256 CUs): four lanes
+//     (AES_BPT_COLUMN, 16 messages per wave);
+//   - else one lane on whole states, 8 blocks (one 128-byte line) per load
+//     and store.
+// The latter two on the 4-table placement (one workgroup per CU), with
+// workgroups just large enough to give every CU the same number of waves, up
+// to 1024 threads, so a short list still spreads over all CUs instead of
+// filling a few.
 aes_variant cbc_msgs_default(size_t nmsgs, int cus)
 {
     const uint64_t c = cus > 0 ? (uint64_t)cus : 256u;
+    if (nmsgs <= 72u * c)
+        return aes_variant{kCbcRow, 0, AES_PLACEMENT_TTABLE4, 0};
     const bool quads = (nmsgs + 63u) / 64u < 8u * c;
     const uint64_t waves = quads ? (nmsgs + 15u) / 16u : (nmsgs + 63u) / 64u;
     const uint64_t per_cu = (waves + c - 1) / c;

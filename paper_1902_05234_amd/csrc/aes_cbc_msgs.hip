@@ -525,6 +525,8 @@ hipError_t launch_cbc_encrypt_msgs(const LaunchShape& shape, int placement, int 
                                    const void* in, uint64_t in_blocks, void* out, uint64_t out_blocks,
                                    uint32_t* rejected, const RoundKeys& rk, int cus, hipStream_t stream)
 {
+    if (shape.bpt == kCbcRow)
+        return launch_cbc_enc_row(nr, msgs, nmsgs, in, in_blocks, out, out_blocks, rejected, rk, cus, stream);
     const CbcMsg* m = static_cast<const CbcMsg*>(msgs);
     switch (placement) {
     case kPlace4:

@@ -32,4 +32,12 @@ hipError_t launch_cbc_dec_flat(int nr, const void* msgs, uint64_t nmsgs, const v
                                void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, int cus,
                                hipStream_t stream);
 
+// Encryption with sixteen lanes per message (aes_cbc_enc_row.hip):
+// launch_cbc_encrypt_msgs with shape.bpt = kCbcRow, its own workgroup size
+// and grid.
+constexpr int kCbcRow = -2;
+hipError_t launch_cbc_enc_row(int nr, const void* msgs, uint64_t nmsgs, const void* in, uint64_t in_blocks,
+                              void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, int cus,
+                              hipStream_t stream);
+
 }  // namespace aesgpu

@@ -422,3 +422,38 @@ def test_decrypt_default_over_set_shapes(oracle_lib, name):
     run_dec(ks, recs, src_dev, out, rejected=rej)
     assert int(rej.item()) == bad.sum()
     assert first_mismatch(to_host(out), want.reshape(-1)) is None
+
+
+@pytest.mark.parametrize("n,max_blocks,keybits,one_arena", [
+    (1, 9, 128, False), (3, 16, 192, False), (4, 17, 256, True), (5, 33, 128, False), (67, 50, 192, True),
+    (1030, 26, 256, False), (17001, 3, 128, False), (19001, 3, 192, False)])
+def test_encrypt_default_over_list_lengths(oracle_lib, n, max_blocks, keybits, one_arena):
+    """The default encryption at list lengths around a wave's four messages,
+    lengths around the 8-block groups, refused records between, more than 16
+    waves per CU, and just past the sixteen-lane kernel's range."""
+    torch = cuda()
+    g = inputs.rng(12, n)
+    key = inputs.random_key(890 + n, keybits)
+    ks = aes.aes_expand_key(key)
+    recs = np.zeros(n, dtype=aes.CBC_MSG_DTYPE)
+    recs["nblocks"] = np.arange(max_blocks, max_blocks - n, -1) % (max_blocks + 1)
+    recs["in_block"] = np.arange(n) * max_blocks
+    recs["out_block"] = recs["in_block"] if one_arena else g.permutation(n) * max_blocks
+    recs["iv"] = g.integers(0, 256, (n, 16))
+    bad = np.zeros(n, dtype=bool)
+    bad[4::58] = bad[33::58] = True
+    recs["reserved"][4::58] = 7
+    recs["out_block"][33::58] = n * max_blocks
+    recs["nblocks"][33::58] = 1
+    src = inputs.random_bytes(891 + n, 16 * n * max_blocks)
+    src_dev = to_dev(src)
+    out = src_dev if one_arena else torch.full((src.size,), SENTINEL, dtype=torch.uint8, device="cuda")
+    want = src.copy() if one_arena else np.full_like(src, SENTINEL)
+    for r in recs[~bad]:
+        a, size, o = (16 * int(r[f]) for f in ("in_block", "nblocks", "out_block"))
+        if size:
+            want[o:o + size] = oracle_lib.cbc_encrypt(key, r["iv"].tobytes(), src[a:a + size])
+    rej = torch.zeros(1, dtype=torch.int32, device="cuda")
+    run(ks, recs, src_dev, out, rejected=rej)
+    assert int(rej.item()) == bad.sum()
+    assert first_mismatch(to_host(out), want) is None
