@@ -47,13 +47,20 @@ static_assert(sizeof(CbcMsg) == 48, "aes_cbc_msg layout");
 
 __device__ __forceinline__ uint4 xor4m(uint4 a, uint4 b) { return make_uint4(a.x ^ b.x, a.y ^ b.y, a.z ^ b.z, a.w ^ b.w); }
 
+// Blocks first .. first + G - 1 of a message of nb > 0 blocks, the last block
+// in the place of any past the end: every load is unconditional, because one
+// under a condition of its own is waited for before the next is issued.
 template <int G>
 __device__ __forceinline__ void load_group(uint4 (&v)[G], const uint4* src, uint64_t first, uint64_t nb)
 {
+    if (first >= nb)
+        first = nb - 1;
+    const uint64_t rest = nb - 1 - first;
+    const uint32_t top = rest < G ? (uint32_t)rest : (uint32_t)G;
+    src += first;
 #pragma unroll
     for (int k = 0; k < G; ++k)
-        if (first + k < nb)
-            v[k] = src[first + k];
+        v[k] = src[(uint32_t)k < top ? (uint32_t)k : top];
 }
 
 // Variant bpt of the one-wave-per-message decryption kernel: kWaveMsg plus
@@ -101,7 +108,8 @@ __global__ __launch_bounds__(1024) void cbc_enc_msgs_kernel(const CbcMsg* __rest
             }
         }
         uint4 cur[G];
-        load_group<G>(cur, src, 0, nb);
+        if (nb != 0)
+            load_group<G>(cur, src, 0, nb);
         // each lane walks its own chain; lanes whose message has ended idle
         // until the wave's longest message is done
         for (uint64_t g = 0; g < nb; g += G) {
@@ -169,16 +177,19 @@ __global__ __launch_bounds__(1024) void cbc_enc_msgs_col_kernel(const CbcMsg* __
         }
         // a quad's lanes share nb, so a quad is wholly active or wholly idle
         uint32_t cur[kColGroup];
+        if (nb != 0) {
+            const uint32_t top = nb < kColGroup ? (uint32_t)nb - 1u : kColGroup - 1u;
 #pragma unroll
-        for (int k = 0; k < kColGroup; ++k)
-            if ((uint64_t)k < nb)
-                cur[k] = src[4u * k];
+            for (int k = 0; k < kColGroup; ++k)
+                cur[k] = src[4u * ((uint32_t)k < top ? (uint32_t)k : top)];
+        }
         for (uint64_t g = 0; g < nb; g += kColGroup) {
+            // unconditional loads, as in load_group
+            const uint32_t top = (nb - g < 2u * kColGroup ? (uint32_t)(nb - g) : 2u * kColGroup) - 1u;
             uint32_t nxt[kColGroup];
 #pragma unroll
             for (int k = 0; k < kColGroup; ++k)
-                if (g + kColGroup + k < nb)
-                    nxt[k] = src[4u * (g + kColGroup + k)];
+                nxt[k] = src[4u * (g + ((uint32_t)(kColGroup + k) < top ? (uint32_t)(kColGroup + k) : top))];
 #pragma unroll
             for (int k = 0; k < kColGroup; ++k) {
                 if (k == 0 || g + k < nb) {
@@ -236,7 +247,8 @@ __global__ __launch_bounds__(1024) void cbc_dec_msgs_kernel(const CbcMsg* __rest
             }
         }
         uint4 cur[G];
-        load_group<G>(cur, src, 0, nb);
+        if (nb != 0)
+            load_group<G>(cur, src, 0, nb);
         for (uint64_t g = 0; g < nb; g += G) {
             uint4 nxt[G];
             load_group<G>(nxt, src, g + G, nb);
