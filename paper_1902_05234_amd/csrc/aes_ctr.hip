@@ -32,19 +32,19 @@ __device__ __forceinline__ uint4 xor4(uint4 a, uint4 b) { return make_uint4(a.x 
 // round 1 (eq 26) byte 15 feeds one lookup, T3 of output column 0; the
 // other 15 lookups and output columns 1..3 are the same for the whole unit.
 // In round 2 every output column then has exactly one lookup that depends
-// on the lane (a byte of column 0) and three that do not.  So a unit
-// computes the 27 shared lookups once, as uniform values from the source
-// table in memory (scalar loads: no LDS work), and each lane does 1 + 4
-// lookups in rounds 1-2 instead of 32: 16 Nr - 27 per block, 133 for
-// AES-128 instead of 160.
-
-// T_t[byte t of w] for a uniform w, from the source table (scalar load).
-template <int T>
-__device__ __forceinline__ uint32_t shared_lookup(uint32_t w)
-{
-    const uint32_t v = c_tables.te0[(w >> (8 * T)) & 255u];
-    return T == 0 ? v : (v << (8 * T)) | (v >> (32 - 8 * T));
-}
+// on the lane (a byte of column 0) and three that do not.  The 27 shared
+// lookups of a wave's next 64 units are done side by side, one unit per lane,
+// and handed out as uniform values.  A lane's own 1 + 4 lookups
+// depend, beside its counters' low byte, on column 0 alone, whose other
+// inputs are bytes 0, 5 and 10 of the counter: byte 10 moves every 2^40
+// blocks.  So a lane keeps their four words per block (ctr_lane_words) over
+// the units it walks and renews them only when column 0's shared part or the
+// unit's low byte differs: rounds 1-2 cost a block four XORs and no lookup,
+// 16 Nr - 32 in all, 128 for AES-128 instead of 160.
+// Bound: as ECB, with fewer lookups.  AES-128 1 GiB 632 -> 606 us, 16 MiB 15.3
+// -> 14.5, against a unit's shared lookups as scalar loads and a lane's own
+// five for every block.  (1 GiB takes 3.55 us per lookup of a block and 154
+// us beside them, here as for ECB with 10 and 14 rounds.)
 
 // T_t[byte t of w] for a per-lane w, from the tables of placement PL in LDS.
 template <int PL, int T>
@@ -60,38 +60,42 @@ __device__ __forceinline__ uint32_t lane_lookup(const uint32_t* lds, const LaneB
     return T == 0 ? v : T == 1 ? rotl8(v) : T == 2 ? rotl16(v) : rotl24(v);
 }
 
-// Rounds 1-2 of a unit, shared part: s = counter words 0..2 and word 3 of
+// Rounds 1-2 of a unit, the part its blocks share: w0 .. w3 = state words of
 // the unit's first counter; rk(i) = round-key word i as used in eq 26.
 struct CtrShared {
     uint32_t u0, v0, v1, v2, v3;  // round 1 column 0 without its lane lookup; round 2 without theirs
 };
 
-template <class K>
-__device__ __forceinline__ CtrShared ctr_shared(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, const K& rk)
+template <int PL, class K>
+__device__ __forceinline__ CtrShared ctr_shared(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3,
+                                                const uint32_t* lds, const LaneBases<PL, false>& lb, const K& rk)
 {
     const uint32_t x0 = w0 ^ rk(0), x1 = w1 ^ rk(1), x2 = w2 ^ rk(2), x3 = w3 ^ rk(3);  // byte 15 of x3 unused
+    auto t0 = [&](uint32_t w) { return lane_lookup<PL, 0>(lds, lb, w); };
+    auto t1 = [&](uint32_t w) { return lane_lookup<PL, 1>(lds, lb, w); };
+    auto t2 = [&](uint32_t w) { return lane_lookup<PL, 2>(lds, lb, w); };
+    auto t3 = [&](uint32_t w) { return lane_lookup<PL, 3>(lds, lb, w); };
     CtrShared c;
-    c.u0 = shared_lookup<0>(x0) ^ shared_lookup<1>(x1) ^ shared_lookup<2>(x2) ^ rk(4);
-    const uint32_t u1 = shared_lookup<0>(x1) ^ shared_lookup<1>(x2) ^ shared_lookup<2>(x3) ^ shared_lookup<3>(x0) ^ rk(5);
-    const uint32_t u2 = shared_lookup<0>(x2) ^ shared_lookup<1>(x3) ^ shared_lookup<2>(x0) ^ shared_lookup<3>(x1) ^ rk(6);
-    const uint32_t u3 = shared_lookup<0>(x3) ^ shared_lookup<1>(x0) ^ shared_lookup<2>(x1) ^ shared_lookup<3>(x2) ^ rk(7);
-    c.v0 = shared_lookup<1>(u1) ^ shared_lookup<2>(u2) ^ shared_lookup<3>(u3) ^ rk(8);
-    c.v1 = shared_lookup<0>(u1) ^ shared_lookup<1>(u2) ^ shared_lookup<2>(u3) ^ rk(9);
-    c.v2 = shared_lookup<0>(u2) ^ shared_lookup<1>(u3) ^ shared_lookup<3>(u1) ^ rk(10);
-    c.v3 = shared_lookup<0>(u3) ^ shared_lookup<2>(u1) ^ shared_lookup<3>(u2) ^ rk(11);
+    c.u0 = t0(x0) ^ t1(x1) ^ t2(x2) ^ rk(4);
+    const uint32_t u1 = t0(x1) ^ t1(x2) ^ t2(x3) ^ t3(x0) ^ rk(5);
+    const uint32_t u2 = t0(x2) ^ t1(x3) ^ t2(x0) ^ t3(x1) ^ rk(6);
+    const uint32_t u3 = t0(x3) ^ t1(x0) ^ t2(x1) ^ t3(x2) ^ rk(7);
+    c.v0 = t1(u1) ^ t2(u2) ^ t3(u3) ^ rk(8);
+    c.v1 = t0(u1) ^ t1(u2) ^ t2(u3) ^ rk(9);
+    c.v2 = t0(u2) ^ t1(u3) ^ t3(u1) ^ rk(10);
+    c.v3 = t0(u3) ^ t2(u1) ^ t3(u2) ^ rk(11);
     return c;
 }
 
-// Key-stream block of the lane whose counter has bytes 0..14 of the unit
-// and top byte of word 3 equal to that of w3 (w3: the lane's state word 3).
-template <int NR, int PL, class K>
-__device__ __forceinline__ uint4 ctr_keystream(const CtrShared& c, uint32_t w3, const uint32_t* lds,
-                                               const LaneBases<PL, false>& lb, uint32_t k3, const K& key)
+// A lane's terms of the four columns after round 2: u0 is round 1's column 0
+// without its lane lookup, w3 the lane's state word 3 (its top byte is read).
+template <int PL>
+__device__ __forceinline__ uint4 ctr_lane_words(uint32_t u0, uint32_t w3, const uint32_t* lds,
+                                                const LaneBases<PL, false>& lb, uint32_t k3)
 {
-    const uint32_t a = c.u0 ^ lane_lookup<PL, 3>(lds, lb, w3 ^ k3);  // round 1, column 0
-    const uint4 s = make_uint4(c.v0 ^ lane_lookup<PL, 0>(lds, lb, a), c.v1 ^ lane_lookup<PL, 3>(lds, lb, a),
-                               c.v2 ^ lane_lookup<PL, 2>(lds, lb, a), c.v3 ^ lane_lookup<PL, 1>(lds, lb, a));
-    return crypt_rounds<NR, false, PL, 3>(s, lds, lb, key);
+    const uint32_t a = u0 ^ lane_lookup<PL, 3>(lds, lb, w3 ^ k3);
+    return make_uint4(lane_lookup<PL, 0>(lds, lb, a), lane_lookup<PL, 3>(lds, lb, a),
+                      lane_lookup<PL, 2>(lds, lb, a), lane_lookup<PL, 1>(lds, lb, a));
 }
 
 // One unit the fast path cannot take (the first, when the counters start
@@ -166,6 +170,10 @@ __global__ __launch_bounds__(1024) void ctr_kernel(const uint4* __restrict__ in,
     // rounds 1-2 of the shared part need eq 26's keys as they are (the
     // 2-table kernels receive the inner-round words turned right by 8)
     auto key12 = [&](int i) { return (PL == kPlace2 && i >= 4) ? rotl8(rk.w[i]) : rk.w[i]; };
+    uint4 mine[BPT];  // ctr_lane_words of column 0's shared part `of` and low byte `low`
+    uint32_t of = 0, low = ~0u;
+    CtrShared ahead{};
+    uint32_t turn = 0;
     for (; u < end_full; u += waves_per_grid) {
         const uint64_t first = u * span - d + lane;
         const uint64_t un = u + waves_per_grid;
@@ -175,18 +183,35 @@ __global__ __launch_bounds__(1024) void ctr_kernel(const uint4* __restrict__ in,
             for (int k = 0; k < BPT; ++k)
                 nxt[k] = in[un * span - d + lane + 64u * k];
         }
-        // counter of the unit's slot 0 (its low byte is a multiple of span)
-        const uint64_t lo = base_lo + u * span;
-        const uint64_t hi = c0.hi + (lo < base_lo ? 1u : 0u);
-        const uint32_t w3 = __builtin_bswap32(static_cast<uint32_t>(lo));
-        const CtrShared c = ctr_shared(__builtin_bswap32(static_cast<uint32_t>(hi >> 32)),
-                                       __builtin_bswap32(static_cast<uint32_t>(hi)),
-                                       __builtin_bswap32(static_cast<uint32_t>(lo >> 32)), w3, key12);
+        if ((turn & 63u) == 0) {
+            // the shared words of the wave's next 64 units, one unit per lane
+            // (the low byte of a unit's first counter is a multiple of span)
+            const uint64_t lo = base_lo + (u + lane * waves_per_grid) * span;
+            const uint64_t hi = c0.hi + (lo < base_lo ? 1u : 0u);
+            ahead = ctr_shared<PL>(__builtin_bswap32(static_cast<uint32_t>(hi >> 32)),
+                                   __builtin_bswap32(static_cast<uint32_t>(hi)),
+                                   __builtin_bswap32(static_cast<uint32_t>(lo >> 32)),
+                                   __builtin_bswap32(static_cast<uint32_t>(lo)), lds, lb, key12);
+        }
+        auto of_unit = [&](uint32_t v) {
+            return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), turn & 63u));
+        };
+        const CtrShared c = {of_unit(ahead.u0), of_unit(ahead.v0), of_unit(ahead.v1), of_unit(ahead.v2),
+                             of_unit(ahead.v3)};
+        ++turn;
+        const uint32_t w3 = __builtin_bswap32(static_cast<uint32_t>(base_lo + u * span));
+        if (c.u0 != of || (w3 >> 24) != low) {
+            of = c.u0;
+            low = w3 >> 24;
+            // slot lane + 64k: only byte 15 (bits 24..31 of word 3) moves, with no carry
+#pragma unroll
+            for (int k = 0; k < BPT; ++k)
+                mine[k] = ctr_lane_words<PL>(c.u0, w3 + ((lane + 64u * k) << 24), lds, lb, rk.w[3]);
+        }
 #pragma unroll
         for (int k = 0; k < BPT; ++k) {
-            // slot lane + 64k: only byte 15 (bits 24..31 of word 3) moves, with no carry
-            const uint32_t w3k = w3 + ((lane + 64u * k) << 24);
-            store_block(out + first + 64u * k, xor4(cur[k], ctr_keystream<NR, PL>(c, w3k, lds, lb, rk.w[3], key)));
+            const uint4 s = make_uint4(c.v0 ^ mine[k].x, c.v1 ^ mine[k].y, c.v2 ^ mine[k].z, c.v3 ^ mine[k].w);
+            store_block(out + first + 64u * k, xor4(cur[k], crypt_rounds<NR, false, PL, 3>(s, lds, lb, key)));
         }
 #pragma unroll
         for (int k = 0; k < BPT; ++k)

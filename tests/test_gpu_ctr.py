@@ -122,3 +122,21 @@ def test_ctr_1gib_windows(oracle_lib):
     assert torch.equal(back, xd)
     del c, back, xd
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("bpt,wg,grid,placement", [(1, 64, 1, 0), (1, 64, 3, 1), (2, 128, 1, 2), (4, 64, 1, 0)])
+@pytest.mark.parametrize("keybits", [128, 192, 256])
+def test_words_kept_over_units_are_renewed(oracle_lib, bpt, wg, grid, placement, keybits):
+    """A wave that walks more than 64 units, with a low byte that changes from
+    unit to unit (one and three waves of 64-block units), over counters that
+    carry into byte 10, which round 1 shares over units otherwise."""
+    torch = cuda()
+    n = 16 * 64 * bpt * (wg // 64) * grid * 131 + 7
+    key = inputs.random_key(77, keybits)
+    ks = aes.aes_expand_key(key)
+    iv = (((0xA5 << 64) + (5 << 40)) - 64 * bpt * 40 - 3).to_bytes(16, "big")
+    x = inputs.random_bytes(78 + bpt, n)
+    out = torch.empty(n, dtype=torch.uint8, device="cuda")
+    aes.aes_ctr_crypt_variant(ks.rk_enc, ks.nr, iv, 1, to_dev(x), out,
+                              aes.Variant(bpt=bpt, wg=wg, placement=placement, grid=grid))
+    assert first_mismatch(to_host(out), oracle_lib.ctr_crypt(key, iv, x, offset=1)) is None
