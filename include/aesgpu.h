@@ -141,11 +141,13 @@ int aes_size_bucket(size_t nblocks);
  *   nbytes:       any length; a partial last block uses the leading bytes
  *                 of its key-stream block.  0 is a no-op returning AES_OK.
  * The variant is the encryption entry of the tuning table for
- * ceil(nbytes/16) blocks.  Asynchronous on stream.
+ * ceil(nbytes/16) blocks, or up to 2 MiB one column word per lane where that
+ * entry is a whole-state one.  Asynchronous on stream.
  */
 int aes_ctr_crypt(const uint32_t *rk, int nr, const uint8_t *iv, uint64_t block_offset, const void *in, void *out,
                   size_t nbytes, void *stream);
-/* Same with an explicit variant (AES_EINVAL outside the search space). */
+/* Same with an explicit variant (AES_EINVAL outside the search space: the
+ * whole-state table kernels). */
 int aes_ctr_crypt_variant(const uint32_t *rk, int nr, const uint8_t *iv, uint64_t block_offset, const void *in,
                           void *out, size_t nbytes, const aes_variant *variant, void *stream);
 

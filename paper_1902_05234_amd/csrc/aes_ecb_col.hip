@@ -68,19 +68,10 @@ hipError_t launch_col_one(const void* in, void* out, uint64_t nblocks, const Rou
                           int cus, hipStream_t stream)
 {
     auto kern = ecb_col_kernel<NR, kDecrypt, PL>;
-    int grid = shape.grid;
-    if (grid <= 0) {
-        int per_cu = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern),
-                                                                    shape.wg, 0);
-        if (e != hipSuccess)
-            return e;
-        grid = cus * (per_cu > 0 ? per_cu : 1);
-    }
-    const uint64_t per_group = (uint64_t)shape.wg / 4u;  // blocks per workgroup per unit
-    const uint64_t needed = (nblocks + per_group - 1) / per_group;
-    if ((uint64_t)grid > needed)
-        grid = (int)needed;
+    int grid = 0;
+    hipError_t e = col_grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
+    if (e != hipSuccess)
+        return e;
     hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint32_t*>(in),
                        static_cast<uint32_t*>(out), nblocks, rk);
     return hipGetLastError();

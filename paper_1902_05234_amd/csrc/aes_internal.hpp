@@ -54,6 +54,9 @@ struct Counter128 {
     uint64_t lo;
 };
 
+// Variant aes_ctr_crypt takes for nblocks blocks (aes_abi.cpp).
+aes_variant ctr_variant(int nr, uint64_t nblocks);
+
 // CTR over nbytes (any length): data block j is XORed with the cipher of
 // counter c0 + j (mod 2^128).  rk is the encryption schedule.
 hipError_t launch_ctr(const LaunchShape& shape, int placement, int nr, const void* in, void* out, uint64_t nbytes,

@@ -111,3 +111,26 @@ def test_cbc_1gib_windows(oracle_lib):
         assert_same(to_host(p[s:s + MiB]), oracle_lib.cbc_decrypt(key, piv, cs), "window at %d" % s)
     del p, cd
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("placement", [0, 1, 2])
+@pytest.mark.parametrize("keybits", [128, 192, 256])
+def test_column_form_around_a_wave_unit(oracle_lib, keybits, placement):
+    """One column word per lane, on every table placement: block counts around
+    a wave's 16 blocks, and enough of them that waves walk several units."""
+    torch = cuda()
+    key = inputs.random_key(640 + placement, keybits)
+    ks = aes.aes_expand_key(key)
+    iv = inputs.random_bytes(641, 16).tobytes()
+    for n in (1, 2, 15, 16, 17, 33, 32768):
+        old = aes.aes_tune_get(ks.nr, True, n)
+        x = inputs.random_bytes(642 + n, 16 * n)
+        out = torch.full((16 * n + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        try:
+            aes.aes_tune_set(ks.nr, True, n, aes.Variant(aes.AES_BPT_COLUMN, 64 if n < 32768 else 1024, placement))
+            aes.aes_cbc_decrypt(ks.rk_dec, ks.nr, iv, to_dev(x), out, nblocks=n)
+        finally:
+            aes.aes_tune_set(ks.nr, True, n, old)
+        got = to_host(out)
+        assert first_mismatch(got[:16 * n], oracle_lib.cbc_decrypt(key, iv, x)) is None, n
+        assert (got[16 * n:] == 0xA5).all(), n

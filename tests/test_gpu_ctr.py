@@ -140,3 +140,29 @@ def test_words_kept_over_units_are_renewed(oracle_lib, bpt, wg, grid, placement,
     aes.aes_ctr_crypt_variant(ks.rk_enc, ks.nr, iv, 1, to_dev(x), out,
                               aes.Variant(bpt=bpt, wg=wg, placement=placement, grid=grid))
     assert first_mismatch(to_host(out), oracle_lib.ctr_crypt(key, iv, x, offset=1)) is None
+
+
+@pytest.mark.parametrize("placement", [0, 1, 2])
+@pytest.mark.parametrize("keybits", [128, 192, 256])
+def test_column_form_every_partial_word_and_unit(oracle_lib, keybits, placement):
+    """One column word per lane: every length around a word, a block and a
+    wave's 16 blocks, several units per wave, counters that carry, in place."""
+    torch = cuda()
+    key = inputs.random_key(630 + placement, keybits)
+    ks = aes.aes_expand_key(key)
+    iv = (2**128 - 2**64 - 3).to_bytes(16, "big")
+    small = aes.aes_tune_get(ks.nr, False, 1)
+    try:
+        aes.aes_tune_set(ks.nr, False, 1, aes.Variant(aes.AES_BPT_COLUMN, 64, placement))
+        for n in [*range(1, 37), 255, 256, 258, 261, 4095]:
+            x = inputs.random_bytes(631 + n, n)
+            buf = torch.full((n + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+            buf[:n] = to_dev(x)
+            aes.aes_ctr_crypt(ks.rk_enc, ks.nr, iv, 2**64 - 9, buf, buf, nbytes=n)
+            got = to_host(buf)
+            assert_same(got[:n], oracle_lib.ctr_crypt(key, iv, x, offset=2**64 - 9), "n=%d" % n)
+            assert (got[n:] == 0xA5).all(), "bytes past the end written, n=%d" % n
+    finally:
+        aes.aes_tune_set(ks.nr, False, 1, small)
+    x = inputs.random_bytes(632, 2 * MiB - 5)  # the largest size of this form: waves walk several units
+    assert_same(to_host(gpu_ctr(ks, iv, to_dev(x))), oracle_lib.ctr_crypt(key, iv, x), "2 MiB - 5")
