@@ -70,6 +70,10 @@ _c_sz = ctypes.c_size_t
 _c_i = ctypes.c_int
 _u32p = ctypes.POINTER(ctypes.c_uint32)
 _u8p = ctypes.POINTER(ctypes.c_uint8)
+# read-only inputs of the calls that a small buffer's time depends on: round
+# keys, counter blocks and IVs go over as bytes objects (0.1 us, where a typed
+# pointer of an array takes 1.2)
+_in_p = ctypes.c_void_p
 
 
 def library_path() -> str:
@@ -93,20 +97,20 @@ def _lib() -> ctypes.CDLL:
                 "aes_last_error": ([], ctypes.c_char_p),
                 "aes_expand_key": ([_u8p, _c_i, _u32p, _u32p, ctypes.POINTER(_c_i)], _c_i),
                 "aes_key_slot": ([_u8p, _c_i, _u32p], _c_i),
-                "aes_ecb_encrypt": ([_u32p, _c_i, _c_p, _c_p, _c_sz, _c_p], _c_i),
-                "aes_ecb_decrypt": ([_u32p, _c_i, _c_p, _c_p, _c_sz, _c_p], _c_i),
-                "aes_ecb_crypt_variant": ([_u32p, _c_i, _c_i, _c_p, _c_p, _c_sz, ctypes.POINTER(_Variant), _c_p], _c_i),
-                "aes_ctr_crypt": ([_u32p, _c_i, _u8p, ctypes.c_uint64, _c_p, _c_p, _c_sz, _c_p], _c_i),
-                "aes_ctr_crypt_variant": ([_u32p, _c_i, _u8p, ctypes.c_uint64, _c_p, _c_p, _c_sz,
+                "aes_ecb_encrypt": ([_in_p, _c_i, _c_p, _c_p, _c_sz, _c_p], _c_i),
+                "aes_ecb_decrypt": ([_in_p, _c_i, _c_p, _c_p, _c_sz, _c_p], _c_i),
+                "aes_ecb_crypt_variant": ([_in_p, _c_i, _c_i, _c_p, _c_p, _c_sz, ctypes.POINTER(_Variant), _c_p], _c_i),
+                "aes_ctr_crypt": ([_in_p, _c_i, _in_p, ctypes.c_uint64, _c_p, _c_p, _c_sz, _c_p], _c_i),
+                "aes_ctr_crypt_variant": ([_in_p, _c_i, _in_p, ctypes.c_uint64, _c_p, _c_p, _c_sz,
                                            ctypes.POINTER(_Variant), _c_p], _c_i),
-                "aes_cbc_decrypt": ([_u32p, _c_i, _u8p, _c_p, _c_p, _c_sz, _c_p], _c_i),
-                "aes_cbc_decrypt_variant": ([_u32p, _c_i, _u8p, _c_p, _c_p, _c_sz, ctypes.POINTER(_Variant), _c_p],
+                "aes_cbc_decrypt": ([_in_p, _c_i, _in_p, _c_p, _c_p, _c_sz, _c_p], _c_i),
+                "aes_cbc_decrypt_variant": ([_in_p, _c_i, _in_p, _c_p, _c_p, _c_sz, ctypes.POINTER(_Variant), _c_p],
                                             _c_i),
-                "aes_cbc_encrypt_msgs": ([_u32p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_p], _c_i),
-                "aes_cbc_encrypt_msgs_variant": ([_u32p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p,
+                "aes_cbc_encrypt_msgs": ([_in_p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_p], _c_i),
+                "aes_cbc_encrypt_msgs_variant": ([_in_p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p,
                                                   ctypes.POINTER(_Variant), _c_p], _c_i),
-                "aes_cbc_decrypt_msgs": ([_u32p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_p], _c_i),
-                "aes_cbc_decrypt_msgs_variant": ([_u32p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p,
+                "aes_cbc_decrypt_msgs": ([_in_p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_p], _c_i),
+                "aes_cbc_decrypt_msgs_variant": ([_in_p, _c_i, _c_p, _c_sz, _c_p, _c_sz, _c_p, _c_sz, _c_p,
                                                   ctypes.POINTER(_Variant), _c_p], _c_i),
                 "aes_tune_set": ([_c_i, _c_i, _c_sz, ctypes.POINTER(_Variant)], _c_i),
                 "aes_tune_get": ([_c_i, _c_i, _c_sz, ctypes.POINTER(_Variant)], _c_i),
@@ -158,10 +162,19 @@ def _check(rc: int):
         raise AesError(rc, aes_last_error())
 
 
+def _current_stream() -> int:
+    """Handle of the current stream, straight from torch's binding where this
+    torch has it (0.1 us; building the Stream object around it takes 2.7)."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(device())
+
+
 def _stream_handle(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -175,18 +188,11 @@ def _bytes_of(t, name: str) -> int:
         raise ValueError("%s must be a device (cuda) tensor" % name)
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def _blocks_of(t, name: str) -> int:
-    import torch
-    if not isinstance(t, torch.Tensor):
-        raise TypeError("%s must be a torch tensor" % name)
-    if not t.is_cuda:
-        raise ValueError("%s must be a device (cuda) tensor" % name)
-    if not t.is_contiguous():
-        raise ValueError("%s must be contiguous" % name)
-    nbytes = t.numel() * t.element_size()
+    nbytes = _bytes_of(t, name)
     if nbytes % 16:
         raise ValueError("%s must hold whole 16-byte blocks (%d bytes)" % (name, nbytes))
     return nbytes // 16
@@ -197,6 +203,11 @@ def _u32_array(a, n=None) -> np.ndarray:
     if n is not None and a.size < n:
         raise ValueError("round-key array too short")
     return a
+
+
+def _rk_bytes(rk, nr: int) -> bytes:
+    """A schedule of at least 4 * (nr + 1) words, for an _in_p argument."""
+    return _u32_array(rk, 4 * (nr + 1)).tobytes()
 
 
 # --------------------------------------------------------------- key schedule
@@ -237,8 +248,8 @@ def _crypt(fn, rk, nr, inp, out, nblocks, stream):
     nblocks = n_in if nblocks is None else int(nblocks)
     if nblocks < 0 or nblocks > n_in or nblocks > n_out:
         raise ValueError("nblocks=%d is negative or exceeds a buffer (in %d, out %d blocks)" % (nblocks, n_in, n_out))
-    rk = _u32_array(rk, 4 * (int(nr) + 1))
-    _check(fn(rk.ctypes.data_as(_u32p), int(nr), inp.data_ptr(), out.data_ptr(), nblocks, _stream_handle(stream)))
+    nr = int(nr)
+    _check(fn(_rk_bytes(rk, nr), nr, inp.data_ptr(), out.data_ptr(), nblocks, _stream_handle(stream)))
     return out
 
 
@@ -269,9 +280,8 @@ def _ctr(fn, rk, nr, iv, block_offset, inp, out, nbytes, stream, *extra):
     iv = bytes(iv)
     if len(iv) != 16:
         raise ValueError("the counter block is 16 bytes, got %d" % len(iv))
-    rk = _u32_array(rk, 4 * (int(nr) + 1))
-    ivb = (ctypes.c_uint8 * 16).from_buffer_copy(iv)
-    _check(fn(rk.ctypes.data_as(_u32p), int(nr), ivb, int(block_offset) & (2**64 - 1), inp.data_ptr(),
+    nr = int(nr)
+    _check(fn(_rk_bytes(rk, nr), nr, iv, int(block_offset) & (2**64 - 1), inp.data_ptr(),
               out.data_ptr(), nbytes, *extra, _stream_handle(stream)))
     return out
 
@@ -297,9 +307,8 @@ def _cbc(fn, rk, nr, iv, inp, out, nblocks, stream, *extra):
     iv = bytes(iv)
     if len(iv) != 16:
         raise ValueError("the initialisation vector is 16 bytes, got %d" % len(iv))
-    rk = _u32_array(rk, 4 * (int(nr) + 1))
-    ivb = (ctypes.c_uint8 * 16).from_buffer_copy(iv)
-    _check(fn(rk.ctypes.data_as(_u32p), int(nr), ivb, inp.data_ptr(), out.data_ptr(), nblocks, *extra,
+    nr = int(nr)
+    _check(fn(_rk_bytes(rk, nr), nr, iv, inp.data_ptr(), out.data_ptr(), nblocks, *extra,
               _stream_handle(stream)))
     return out
 
@@ -346,8 +355,8 @@ def _cbc_msgs(fn, fn_variant, rk, nr, msgs_dev, nmsgs, in_base, out_base, reject
         if _bytes_of(rejected_dev, "rejected_dev") < 4:
             raise ValueError("the rejected counter needs 4 bytes")
         rej = rejected_dev.data_ptr()
-    rk = _u32_array(rk, 4 * (int(nr) + 1))
-    args = [rk.ctypes.data_as(_u32p), int(nr), msgs_dev.data_ptr(), nmsgs, in_base.data_ptr(),
+    nr = int(nr)
+    args = [_rk_bytes(rk, nr), nr, msgs_dev.data_ptr(), nmsgs, in_base.data_ptr(),
             _blocks_of(in_base, "in_base"), out_base.data_ptr(), _blocks_of(out_base, "out_base"), rej]
     if variant is None:
         _check(fn(*args, _stream_handle(stream)))
@@ -378,32 +387,33 @@ def expand_key(key: bytes) -> KeySchedule:
     return aes_expand_key(key)
 
 
+def _like(x):
+    import torch
+    return torch.empty_like(x)
+
+
 def ecb_encrypt(ks: KeySchedule, x, out=None, stream=None):
     """Encrypt a uint8 CUDA tensor of whole blocks; returns ``out``."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     return aes_ecb_encrypt(ks.rk_enc, ks.nr, x, out, stream=stream)
 
 
 def ecb_decrypt(ks: KeySchedule, x, out=None, stream=None):
     """Decrypt a uint8 CUDA tensor of whole blocks; returns ``out``."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     return aes_ecb_decrypt(ks.rk_dec, ks.nr, x, out, stream=stream)
 
 
 def ctr_crypt(ks: KeySchedule, iv: bytes, x, out=None, block_offset: int = 0, stream=None):
     """CTR over a uint8 CUDA tensor of any length; returns ``out``."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     return aes_ctr_crypt(ks.rk_enc, ks.nr, iv, block_offset, x, out, stream=stream)
 
 
 def cbc_decrypt(ks: KeySchedule, iv: bytes, x, out=None, stream=None):
     """CBC decryption of a uint8 CUDA tensor of whole blocks into a separate
     ``out`` (in place is refused: block b reads ciphertext block b - 1)."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     return aes_cbc_decrypt(ks.rk_dec, ks.nr, iv, x, out, stream=stream)
 
 
@@ -419,16 +429,14 @@ def cbc_encrypt_msgs(ks: KeySchedule, recs, x, out=None, stream=None):
     """CBC encryption of the message set ``recs`` (a host numpy array of
     CBC_MSG_DTYPE records, or a device uint8 tensor holding them) from the
     uint8 CUDA tensor ``x`` into ``out`` (a new tensor like ``x`` if None)."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     msgs, n = _msgs_on_device(recs, x)
     return aes_cbc_encrypt_msgs(ks.rk_enc, ks.nr, msgs, n, x, out, stream=stream)
 
 
 def cbc_decrypt_msgs(ks: KeySchedule, recs, x, out=None, stream=None):
     """CBC decryption of the message set ``recs`` (as cbc_encrypt_msgs)."""
-    import torch
-    out = torch.empty_like(x) if out is None else out
+    out = _like(x) if out is None else out
     msgs, n = _msgs_on_device(recs, x)
     return aes_cbc_decrypt_msgs(ks.rk_dec, ks.nr, msgs, n, x, out, stream=stream)
 
@@ -696,7 +704,7 @@ def _pipe_sigs(lib):
     lib.aes_pipe_create.restype = _c_i
     lib.aes_pipe_destroy.argtypes = [_c_p]
     lib.aes_pipe_destroy.restype = _c_i
-    lib.aes_pipe_run.argtypes = [_c_p, _c_i, _u32p, _c_i, _u8p, _c_p, _c_p, _c_sz, _c_i]
+    lib.aes_pipe_run.argtypes = [_c_p, _c_i, _in_p, _c_i, _in_p, _c_p, _c_p, _c_sz, _c_i]
     lib.aes_pipe_run.restype = _c_i
     lib._pipe_sigs = True
 
@@ -749,15 +757,14 @@ class HostPipe:
         if on < sn:
             raise ValueError("out holds %d bytes, src %d" % (on, sn))
         rk = ks.rk_dec if op == AES_PIPE_ECB_DECRYPT else ks.rk_enc
-        rk = _u32_array(rk, 4 * (ks.nr + 1))
         ivb = None
         if op == AES_PIPE_CTR:
             iv = bytes(iv if iv is not None else bytes(16))
             if len(iv) != 16:
                 raise ValueError("the counter block is 16 bytes")
-            ivb = (ctypes.c_uint8 * 16).from_buffer_copy(iv)
+            ivb = iv
         flags = AES_PIPE_HOST_PINNED if (spin and opin) else 0
-        _check(self._lib.aes_pipe_run(self._h, int(op), rk.ctypes.data_as(_u32p), int(ks.nr), ivb, sp, op_, sn, flags))
+        _check(self._lib.aes_pipe_run(self._h, int(op), _rk_bytes(rk, ks.nr), int(ks.nr), ivb, sp, op_, sn, flags))
         return out
 
     def close(self):
