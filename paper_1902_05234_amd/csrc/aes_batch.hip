@@ -26,12 +26,10 @@
 #include <atomic>
 #include <cstdint>
 #include <mutex>
-#include <type_traits>
 
 #include "aes_batch_signal.hpp"
 #include "aes_device.hpp"
 #include "aes_internal.hpp"
-#include "aes_launch.hpp"
 
 namespace aesgpu {
 
@@ -244,34 +242,29 @@ hipError_t batch_groups_per_cu(int bpt, int placement, int wg, int* per_cu)
 
 namespace {
 
-template <auto K>
-struct Kernel {
-    static constexpr auto value = K;
-};
-
 hipError_t launch_batch_impl(const BatchArgs& a, int bpt, int placement, int grid, int wg, uint32_t* done_word,
                              uint32_t seq, hipStream_t stream)
 {
-    auto go = [&](auto kern) {
-        return launch_kernel<decltype(kern)::value>(
-            grid, wg, stream, a.items, a.n_enc, a.n_dec, a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base),
-            static_cast<uint4*>(a.out_base), a.in_blocks, a.out_blocks, a.counters, a.enc_groups, done_word, seq);
-    };
-    auto of_bpt = [&](auto place) {
-        constexpr int pl = decltype(place)::value;
-        switch (bpt) {
-        case 1: return go(Kernel<batch_kernel<1, pl>>{});
-        case 2: return go(Kernel<batch_kernel<2, pl>>{});
-        case 4: return go(Kernel<batch_kernel<4, pl>>{});
-        default: return hipErrorInvalidValue;
-        }
-    };
+#define AESGPU_BATCH_LAUNCH(B, P)                                                                                  \
+    hipLaunchKernelGGL((batch_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, a.n_enc, a.n_dec,           \
+                       a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base), static_cast<uint4*>(a.out_base), \
+                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, done_word, seq)
+#define AESGPU_BATCH_PLACEMENT(P)                   \
+    switch (bpt) {                                  \
+    case 1: AESGPU_BATCH_LAUNCH(1, P); break;       \
+    case 2: AESGPU_BATCH_LAUNCH(2, P); break;       \
+    case 4: AESGPU_BATCH_LAUNCH(4, P); break;       \
+    default: return hipErrorInvalidValue;           \
+    }
     switch (placement) {
-    case kPlace4: return of_bpt(std::integral_constant<int, kPlace4>{});
-    case kPlace2: return of_bpt(std::integral_constant<int, kPlace2>{});
-    case kPlace1: return of_bpt(std::integral_constant<int, kPlace1>{});
+    case kPlace4: AESGPU_BATCH_PLACEMENT(kPlace4); break;
+    case kPlace2: AESGPU_BATCH_PLACEMENT(kPlace2); break;
+    case kPlace1: AESGPU_BATCH_PLACEMENT(kPlace1); break;
     default: return hipErrorInvalidValue;
     }
+#undef AESGPU_BATCH_PLACEMENT
+#undef AESGPU_BATCH_LAUNCH
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -345,7 +338,8 @@ hipError_t launch_batch_noalloc(BatchArgs a, int bpt, int placement, int grid, i
     if (e != hipSuccess)
         return e;
     // the counters start at zero whatever an earlier launch left
-    e = launch_kernel<zero_words>(1, 64, stream, p, 4u);
+    hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, p, 4u);
+    e = hipGetLastError();
     if (e != hipSuccess)
         return e;
     a.counters = p;

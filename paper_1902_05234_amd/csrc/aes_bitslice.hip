@@ -308,14 +308,15 @@ template <int NR, bool kDecrypt>
 hipError_t launch_bs_one(const void* in, void* out, uint64_t nblocks, const RoundKeys& rk, int wg, int grid_req,
                          int cus, hipStream_t stream)
 {
-    constexpr auto kern = bitslice_kernel<NR, kDecrypt>;
+    auto kern = bitslice_kernel<NR, kDecrypt>;
     const LaunchShape shape{kSlicedBlocks, wg, grid_req};
     int grid = 0;
     hipError_t e = grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, wg, stream, static_cast<const uint4*>(in), static_cast<uint4*>(out),
-                               nblocks, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(wg), 0, stream, static_cast<const uint4*>(in), static_cast<uint4*>(out),
+                       nblocks, rk);
+    return hipGetLastError();
 }
 
 hipError_t launch_bitslice(const LaunchShape& shape, int nr, bool decrypt, const void* in, void* out,

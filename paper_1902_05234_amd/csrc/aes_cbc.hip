@@ -124,26 +124,28 @@ template <int NR, int PL>
 hipError_t launch_cbc_col(const void* in, void* out, uint64_t nblocks, const uint4& iv, const RoundKeys& rk,
                           const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_dec_col_kernel<NR, PL>;
+    auto kern = cbc_dec_col_kernel<NR, PL>;
     int grid = 0;
     hipError_t e = col_grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint32_t*>(in),
-                               static_cast<uint32_t*>(out), nblocks, iv, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint32_t*>(in),
+                       static_cast<uint32_t*>(out), nblocks, iv, rk);
+    return hipGetLastError();
 }
 
 template <int NR, int BPT, int PL>
 hipError_t launch_cbc_one(const void* in, void* out, uint64_t nblocks, const uint4& iv, const RoundKeys& rk,
                           const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_dec_kernel<NR, BPT, PL>;
+    auto kern = cbc_dec_kernel<NR, BPT, PL>;
     int grid = 0;
     hipError_t e = grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint4*>(in), static_cast<uint4*>(out),
-                               nblocks, iv, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint4*>(in),
+                       static_cast<uint4*>(out), nblocks, iv, rk);
+    return hipGetLastError();
 }
 
 template <int BPT, int PL>

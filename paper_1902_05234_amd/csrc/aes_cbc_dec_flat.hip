@@ -186,9 +186,10 @@ hipError_t launch_flat(const FlatMsg* msgs, uint64_t nmsgs, uint32_t per_group, 
     const uint64_t units = (nmsgs + per_group - 1) / per_group * slices;
     const uint64_t waves = (uint64_t)wg / 64u;
     const uint64_t grid = std::min<uint64_t>((uint64_t)max_grid, (units + waves - 1) / waves);
-    return launch_kernel<cbc_dec_flat_kernel<NR, PL>>((uint32_t)grid, wg, stream, msgs, nmsgs, per_group,
-                                                      slices, static_cast<const uint4*>(in), in_blocks,
-                                                      static_cast<uint4*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL((cbc_dec_flat_kernel<NR, PL>), dim3((uint32_t)grid), dim3(wg), 0, stream, msgs, nmsgs,
+                       per_group, slices, static_cast<const uint4*>(in), in_blocks, static_cast<uint4*>(out),
+                       out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 }  // namespace

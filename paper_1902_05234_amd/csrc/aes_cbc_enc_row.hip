@@ -37,7 +37,6 @@
 
 #include "aes_cbc_msgs.hpp"
 #include "aes_device.hpp"
-#include "aes_launch.hpp"
 
 namespace aesgpu {
 
@@ -207,10 +206,10 @@ hipError_t launch_row(const void* msgs, uint64_t nmsgs, const void* in, uint64_t
     const uint64_t c = (uint64_t)cus, waves = (nmsgs + 3u) / 4u, per_cu = (waves + c - 1) / c;
     const uint64_t wg = per_cu <= 16u ? 64u * per_cu : std::min<uint64_t>(1024, 64u * ((per_cu + 1u) / 2u));
     const uint64_t grid = std::min<uint64_t>(2u * c, (waves * 64u + wg - 1) / wg);
-    return launch_kernel<cbc_enc_msgs_row_kernel<NR>>((uint32_t)grid, (uint32_t)wg, stream,
-                                                      static_cast<const RowMsg*>(msgs), nmsgs,
-                                                      static_cast<const uint32_t*>(in), in_blocks,
-                                                      static_cast<uint32_t*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL(cbc_enc_msgs_row_kernel<NR>, dim3((uint32_t)grid), dim3((uint32_t)wg), 0, stream,
+                       static_cast<const RowMsg*>(msgs), nmsgs, static_cast<const uint32_t*>(in), in_blocks,
+                       static_cast<uint32_t*>(out), out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 }  // namespace

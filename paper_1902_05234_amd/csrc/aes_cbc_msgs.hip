@@ -341,7 +341,7 @@ hipError_t launch_one_cbc_dec_msgs_wave(const CbcMsg* msgs, uint64_t nmsgs, cons
                                         void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk,
                                         const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_dec_msgs_wave_kernel<NR, BPT, PL>;
+    auto kern = cbc_dec_msgs_wave_kernel<NR, BPT, PL>;
     int grid = shape.grid;
     if (grid <= 0) {
         int per_cu = 0;
@@ -355,8 +355,9 @@ hipError_t launch_one_cbc_dec_msgs_wave(const CbcMsg* msgs, uint64_t nmsgs, cons
     const uint64_t needed = (nmsgs + per_group - 1) / per_group;
     if ((uint64_t)grid > needed)
         grid = (int)needed;
-    return launch_kernel<kern>(grid, shape.wg, stream, msgs, nmsgs, static_cast<const uint4*>(in), in_blocks,
-                               static_cast<uint4*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, msgs, nmsgs, static_cast<const uint4*>(in),
+                       in_blocks, static_cast<uint4*>(out), out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 template <int NR, int G, int PL>
@@ -364,7 +365,7 @@ hipError_t launch_one_cbc_dec_msgs(const CbcMsg* msgs, uint64_t nmsgs, const voi
                                    uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk,
                                    const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_dec_msgs_kernel<NR, G, PL>;
+    auto kern = cbc_dec_msgs_kernel<NR, G, PL>;
     int grid = shape.grid;
     if (grid <= 0) {
         int per_cu = 0;
@@ -379,8 +380,9 @@ hipError_t launch_one_cbc_dec_msgs(const CbcMsg* msgs, uint64_t nmsgs, const voi
     const uint64_t needed = (waves + per_group - 1) / per_group;
     if ((uint64_t)grid > needed)
         grid = (int)needed;
-    return launch_kernel<kern>(grid, shape.wg, stream, msgs, nmsgs, static_cast<const uint4*>(in), in_blocks,
-                               static_cast<uint4*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, msgs, nmsgs, static_cast<const uint4*>(in),
+                       in_blocks, static_cast<uint4*>(out), out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 template <int G, int PL>
@@ -426,7 +428,7 @@ hipError_t launch_one_cbc_msgs_col(const CbcMsg* msgs, uint64_t nmsgs, const voi
                                    uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk,
                                    const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_enc_msgs_col_kernel<NR, PL>;
+    auto kern = cbc_enc_msgs_col_kernel<NR, PL>;
     int grid = shape.grid;
     if (grid <= 0) {
         int per_cu = 0;
@@ -442,8 +444,9 @@ hipError_t launch_one_cbc_msgs_col(const CbcMsg* msgs, uint64_t nmsgs, const voi
     const uint64_t needed = (waves + per_group - 1) / per_group;
     if ((uint64_t)grid > needed)
         grid = (int)needed;
-    return launch_kernel<kern>(grid, shape.wg, stream, msgs, nmsgs, static_cast<const uint32_t*>(in), in_blocks,
-                               static_cast<uint32_t*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, msgs, nmsgs, static_cast<const uint32_t*>(in),
+                       in_blocks, static_cast<uint32_t*>(out), out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 template <int NR, int G, int PL>
@@ -451,7 +454,7 @@ hipError_t launch_one_cbc_msgs(const CbcMsg* msgs, uint64_t nmsgs, const void* i
                                uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, const LaunchShape& shape,
                                int cus, hipStream_t stream)
 {
-    constexpr auto kern = cbc_enc_msgs_kernel<NR, G, PL>;
+    auto kern = cbc_enc_msgs_kernel<NR, G, PL>;
     int grid = shape.grid;
     if (grid <= 0) {
         int per_cu = 0;
@@ -467,8 +470,9 @@ hipError_t launch_one_cbc_msgs(const CbcMsg* msgs, uint64_t nmsgs, const void* i
     const uint64_t needed = (waves + per_group - 1) / per_group;
     if ((uint64_t)grid > needed)
         grid = (int)needed;
-    return launch_kernel<kern>(grid, shape.wg, stream, msgs, nmsgs, static_cast<const uint4*>(in), in_blocks,
-                               static_cast<uint4*>(out), out_blocks, rejected, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, msgs, nmsgs, static_cast<const uint4*>(in),
+                       in_blocks, static_cast<uint4*>(out), out_blocks, rejected, rk);
+    return hipGetLastError();
 }
 
 template <int G, int PL>

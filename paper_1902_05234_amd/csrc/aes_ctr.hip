@@ -284,26 +284,28 @@ template <int NR, int PL>
 hipError_t launch_ctr_col(const void* in, void* out, uint64_t nbytes, const Counter128& c0, const RoundKeys& rk,
                           const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = ctr_col_kernel<NR, PL>;
+    auto kern = ctr_col_kernel<NR, PL>;
     int grid = 0;
     hipError_t e = col_grid_for(reinterpret_cast<const void*>(kern), shape, cus, (nbytes + 15u) / 16u, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint32_t*>(in),
-                               static_cast<uint32_t*>(out), nbytes, c0, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint32_t*>(in),
+                       static_cast<uint32_t*>(out), nbytes, c0, rk);
+    return hipGetLastError();
 }
 
 template <int NR, int BPT, int PL>
 hipError_t launch_ctr_one(const void* in, void* out, uint64_t nbytes, const Counter128& c0, const RoundKeys& rk,
                           const LaunchShape& shape, int cus, hipStream_t stream)
 {
-    constexpr auto kern = ctr_kernel<NR, BPT, PL>;
+    auto kern = ctr_kernel<NR, BPT, PL>;
     int grid = 0;
     hipError_t e = grid_for(reinterpret_cast<const void*>(kern), shape, cus, (nbytes + 15u) / 16u, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint4*>(in), static_cast<uint4*>(out),
-                               nbytes, c0, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint4*>(in),
+                       static_cast<uint4*>(out), nbytes, c0, rk);
+    return hipGetLastError();
 }
 
 template <int BPT, int PL>

@@ -4,7 +4,6 @@
 #include <cstdint>
 
 #include "aes_internal.hpp"
-#include "aes_launch.hpp"
 
 namespace aesgpu {
 
@@ -43,8 +42,9 @@ __global__ __launch_bounds__(256) void copy_kernel(const uint4* __restrict__ in,
 
 hipError_t launch_copy(const void* in, void* out, uint64_t n16, int grid, hipStream_t stream)
 {
-    return launch_kernel<copy_kernel>(grid, 256, stream, static_cast<const uint4*>(in),
-                                      static_cast<uint4*>(out), n16);
+    hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const uint4*>(in),
+                       static_cast<uint4*>(out), n16);
+    return hipGetLastError();
 }
 
 }  // namespace aesgpu

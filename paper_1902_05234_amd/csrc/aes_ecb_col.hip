@@ -67,13 +67,14 @@ template <int NR, bool kDecrypt, int PL>
 hipError_t launch_col_one(const void* in, void* out, uint64_t nblocks, const RoundKeys& rk, const LaunchShape& shape,
                           int cus, hipStream_t stream)
 {
-    constexpr auto kern = ecb_col_kernel<NR, kDecrypt, PL>;
+    auto kern = ecb_col_kernel<NR, kDecrypt, PL>;
     int grid = 0;
     hipError_t e = col_grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint32_t*>(in),
-                               static_cast<uint32_t*>(out), nblocks, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint32_t*>(in),
+                       static_cast<uint32_t*>(out), nblocks, rk);
+    return hipGetLastError();
 }
 
 template <bool kDecrypt, int PL>

@@ -18,7 +18,6 @@
 
 #include "aes_device.hpp"
 #include "aes_internal.hpp"
-#include "aes_launch.hpp"
 
 namespace aesgpu {
 
@@ -114,13 +113,14 @@ template <int NR, bool kDecrypt, int BPT, int PL>
 hipError_t launch_one(const void* in, void* out, uint64_t nblocks, const RoundKeys& rk, const LaunchShape& shape,
                       int cus, hipStream_t stream)
 {
-    constexpr auto kern = ecb_kernel<NR, kDecrypt, BPT, PL>;
+    auto kern = ecb_kernel<NR, kDecrypt, BPT, PL>;
     int grid = 0;
     hipError_t e = grid_for(reinterpret_cast<const void*>(kern), shape, cus, nblocks, &grid);
     if (e != hipSuccess)
         return e;
-    return launch_kernel<kern>(grid, shape.wg, stream, static_cast<const uint4*>(in), static_cast<uint4*>(out),
-                               nblocks, rk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(shape.wg), 0, stream, static_cast<const uint4*>(in),
+                       static_cast<uint4*>(out), nblocks, rk);
+    return hipGetLastError();
 }
 
 template <bool kDecrypt, int BPT, int PL>

@@ -8,7 +8,6 @@
 // of launch makes its stores visible before this kernel starts, and this
 // kernel's store is a system-scope release, so the word is seen after them.
 #include "aes_host_word.hpp"
-#include "aes_launch.hpp"
 
 namespace aesgpu {
 
@@ -26,7 +25,8 @@ hipError_t launch_host_word(uint32_t* word, uint32_t seq, hipStream_t stream)
 {
     if (word == nullptr)
         return hipErrorInvalidValue;
-    return launch_kernel<host_word_kernel>(1, 64, stream, word, seq);
+    hipLaunchKernelGGL(host_word_kernel, dim3(1), dim3(64), 0, stream, word, seq);
+    return hipGetLastError();
 }
 
 }  // namespace aesgpu
