@@ -376,9 +376,9 @@ typedef struct {
     uint32_t key_slot;
 } aes_work_item;
 
-/* Largest work item, in blocks (256 MiB).  One wave walks an item alone, so
- * items are meant to be small: the batched launch and the serving engine are
- * tuned at 2048-4096 blocks. */
+/* Largest work item, in blocks (256 MiB).  In all but short lists one wave
+ * walks an item alone, so items are meant to be small: the batched launch and
+ * the serving engine are tuned at 2048-4096 blocks. */
 #define AES_MAX_ITEM_BLOCKS (1u << 24)
 
 /*
@@ -399,7 +399,8 @@ typedef struct {
     int32_t bpt;        /* 1, 2, 4 */
     int32_t wg;         /* multiple of 64 in [64, 1024] */
     int32_t grid;       /* 0 = as many workgroups as fit on every compute unit at once */
-    int32_t enc_groups; /* workgroups starting on the encryption list; <0 = by item share */
+    int32_t enc_groups; /* workgroups starting on the encryption list; <0 = by item share (a list
+                           short enough for one item per wave takes its own grid and split) */
     int32_t placement;  /* AES_PLACEMENT_TTABLE4 (0, the default), _TTABLE2 or _TTABLE1 */
 } aes_batch_config;
 

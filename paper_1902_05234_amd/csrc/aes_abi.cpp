@@ -448,9 +448,23 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
     int grid = 0, enc_groups = 0;
     // the item counts stand in for the byte shares (the items live on the device)
     batch_grid(n_enc, n_dec, n_enc, n_enc + n_dec, c.wg, max_grid, c.enc_groups, &grid, &enc_groups);
+    // Fewer items than the device holds waves: claimed in as many parts (up to
+    // 32) as leave every wave one claim at most, so that a short list spreads
+    // over all CUs and nothing goes through the claim counters.
+    const uint64_t per_group = (uint64_t)(c.wg / 64);
+    uint32_t lp = 0;
+    for (uint32_t p = 0; p <= 5u; ++p) {
+        const uint64_t need_e = (((uint64_t)n_enc << p) + per_group - 1) / per_group;
+        const uint64_t need_d = (((uint64_t)n_dec << p) + per_group - 1) / per_group;
+        if (need_e + need_d > (uint64_t)max_grid)
+            break;
+        lp = p;
+        grid = (int)(need_e + need_d);
+        enc_groups = (int)need_e;
+    }
     out->args = BatchArgs{reinterpret_cast<const WorkItem*>(items_dev), (uint32_t)n_enc, (uint32_t)n_dec,
                           key_table_dev, (uint32_t)n_slots, in_base, out_base, (uint64_t)in_blocks,
-                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups};
+                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, lp};
     out->bpt = c.bpt;
     out->wg = c.wg;
     out->grid = grid;

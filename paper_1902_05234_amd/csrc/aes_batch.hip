@@ -2,9 +2,14 @@
 //
 // The host splits every message into work items of at most `chunk` blocks
 // (aes_batch_plan) and lists all encryption items before all decryption
-// items.  Each wave claims one item at a time with an atomic counter, loads
-// that item's round keys as uniform values, and runs the same round core as
-// the plain kernel for the item's key size.
+// items.  Each wave takes one item at a time (the first ones dealt out, the
+// rest claimed with an atomic counter), loads that item's round keys as
+// uniform values, and runs the same round core as the plain kernel for the
+// item's key size.  A list of fewer items than the device holds waves is
+// walked in parts of items, so that it spreads over all CUs.
+// (Time per launch, 4 tables, items of 2048 blocks: 30 messages of up to 1 MiB
+// 83 -> 9.5 us, 1000 of up to 4 KiB 43 -> 9.7, 2000 of up to 8 MiB 1160 ->
+// 1115, against items claimed one by one, each by one wave.)
 //
 // LDS holds the tables of one direction only (4 tables: 128 KiB + 32 KiB of
 // InvS; 2 tables: 64 + 8 KiB; 1 table: 32 + 8 KiB), so the workgroups are
@@ -70,19 +75,53 @@ __device__ __forceinline__ void run_item(const uint4* __restrict__ in, uint4* __
         for (int j = 0; j < BPT; ++j)
             store_block(out + first + 64u * j, x[j]);
     }
-    const uint32_t b0 = full * span;
-    if (b0 < nblocks) {
-#pragma unroll
-        for (int j = 0; j < BPT; ++j) {
-            const uint32_t b = b0 + lane + 64u * j;
-            if (b < nblocks)
-                store_block(out + b, crypt_block<NR, kDecrypt, PL>(in[b], lds, lb, key));
-        }
+    // the rest row by row, with one copy of the rounds in the code: three key
+    // sizes and two directions share the instruction cache
+#pragma unroll 1
+    for (uint32_t row = full * span; row < nblocks; row += 64u) {
+        const uint32_t b = row + lane;
+        if (b < nblocks)
+            store_block(out + b, crypt_block<NR, kDecrypt, PL>(in[b], lds, lb, key));
     }
 }
 
+// How the claims of one list are dealt: 2^lp parts of each item, `waves` waves
+// that start on the list.  The first `dealt` claims go to those waves in turn,
+// the rest to whichever wave asks, through the list's counter.  An update of
+// the counter takes about 14 ns in which no other is served: 1000 items of one
+// unit on 1008 waves took 43 us, the time of their 3000 updates.  So a list
+// that one claim per wave covers is dealt whole, a longer one to five eighths
+// but at most 8 per wave: dealt waves drift apart over the arenas (20,000
+// messages of up to 8 MiB, 104 claims per wave: 9448 us claimed one by one,
+// 9310 so, 9786 with five eighths dealt), and what is left evens out their
+// sums over items of different lengths.
+struct Claims {
+    uint32_t n, dealt;
+};
+
+__device__ __forceinline__ Claims claims_of(uint32_t n_items, uint32_t lp, uint32_t waves)
+{
+    const uint32_t n = n_items << lp;
+    if (n <= waves)
+        return Claims{n, n};
+    const uint32_t rounds = waves != 0 ? n / waves : 0u;
+    return Claims{n, min((rounds % 16u * 5u + 7u) / 8u + rounds / 16u * 8u, 8u) * waves};
+}
+
+// Claims taken with one update of the counter when `left` are left: several
+// while many are, and twice as many as the last time, up to eight times the
+// number for long items, where none of those was over one row of blocks
+// (100,000 messages of up to 1 KiB: 1233 us one by one, 801 with the number
+// for long items, 280 so).
+__device__ __forceinline__ uint32_t claims_at_once(uint32_t left, uint32_t waves, uint32_t taken, uint32_t longest)
+{
+    const uint32_t few = 1u + left / 16u / waves;
+    return longest <= 64u ? max(few, min(2u * taken, 1u + left / 2u / waves)) : few;
+}
+
 template <bool kDecrypt, int BPT, int PL>
-__device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32_t first_item, uint32_t n_items,
+__device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32_t first_item, uint32_t lp,
+                                      const Claims& claims, uint32_t first_claim, uint32_t claim_step,
                                       const uint32_t* __restrict__ key_table, uint32_t n_slots,
                                       const uint4* __restrict__ in_base, uint4* __restrict__ out_base,
                                       uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
@@ -90,31 +129,54 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
 {
     const uint32_t lane = threadIdx.x & 63u;
     const LaneBases<PL, kDecrypt> lb(threadIdx.x);
+    uint32_t dealt = first_claim;  // the wave's next claim among the dealt ones
+    uint32_t next = 0, run = 0, taken = 1, longest = 0;
+    uint32_t left = claims.n - claims.dealt;  // as the wave last saw it
+    uint32_t* const counter = &counters[kDecrypt ? 1 : 0];
     for (;;) {
-        uint32_t idx = 0;
-        if (lane == 0)
-            idx = atomicAdd(&counters[kDecrypt ? 1 : 0], 1u);
-        idx = __builtin_amdgcn_readfirstlane(idx);
-        if (idx >= n_items)
+        uint32_t idx = dealt;
+        if (dealt < claims.dealt) {
+            dealt += claim_step;
+        } else if (claims.dealt < claims.n) {
+            if (run == 0) {
+                run = taken = claims_at_once(left, claim_step, taken, longest);
+                longest = 0;
+                if (lane == 0)
+                    next = claims.dealt + atomicAdd(counter, run);
+                next = __builtin_amdgcn_readfirstlane(next);
+                left = next < claims.n ? claims.n - next : 0u;
+            }
+            idx = next++;
+            --run;
+        }
+        if (idx >= claims.n)
             break;
-        const WorkItem it = items[first_item + idx];
+        const uint32_t part = idx & ((1u << lp) - 1u);
+        const WorkItem it = items[first_item + (idx >> lp)];
         const uint64_t in_b = __builtin_amdgcn_readfirstlane((uint32_t)it.in_block) |
                               ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.in_block >> 32)) << 32);
         const uint64_t out_b = __builtin_amdgcn_readfirstlane((uint32_t)it.out_block) |
                                ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.out_block >> 32)) << 32);
         const uint32_t nb = __builtin_amdgcn_readfirstlane(it.nblocks);
         const uint32_t slot = __builtin_amdgcn_readfirstlane(it.key_slot);
+        longest = max(longest, nb);
         const bool ok = slot < n_slots && nb <= AES_MAX_ITEM_BLOCKS && in_b <= in_blocks && nb <= in_blocks - in_b &&
                         out_b <= out_blocks && nb <= out_blocks - out_b;
         const uint32_t* kp = key_table + (uint64_t)(ok ? slot : 0u) * kSlotWords;
         const int nr = ok ? (int)__builtin_amdgcn_readfirstlane(kp[kSlotNr]) : 0;
         const uint32_t* kd = kp + (kDecrypt ? 64 : 0);
+        // the part's blocks: an equal share, in wave rows of 64 blocks
+        const uint32_t share = lp == 0 ? nb : ((nb + (64u << lp) - 1u) >> (6u + lp)) << 6;
+        const uint32_t from = part * share;  // at most nb + 63 * 2^lp
+        const uint32_t n = from < nb ? (nb - from < share ? nb - from : share) : 0u;
+        const uint4* src = in_base + in_b + from;
+        uint4* dst = out_base + out_b + from;
         switch (nr) {
-        case 10: run_item<10, kDecrypt, BPT, PL>(in_base + in_b, out_base + out_b, nb, lds, lb, kd); break;
-        case 12: run_item<12, kDecrypt, BPT, PL>(in_base + in_b, out_base + out_b, nb, lds, lb, kd); break;
-        case 14: run_item<14, kDecrypt, BPT, PL>(in_base + in_b, out_base + out_b, nb, lds, lb, kd); break;
+        case 10: run_item<10, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
+        case 12: run_item<12, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
+        case 14: run_item<14, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
         default:
-            if (lane == 0)
+            if (lane == 0 && part == 0)
                 atomicAdd(&counters[3], 1u);
             break;
         }
@@ -129,36 +191,63 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPla
                                                      uint32_t n_slots, const uint4* __restrict__ in_base,
                                                      uint4* __restrict__ out_base, uint64_t in_blocks,
                                                      uint64_t out_blocks, uint32_t* counters, uint32_t enc_groups,
-                                                     uint32_t* done_word, uint32_t done_seq)
+                                                     uint32_t lp, uint32_t* done_word, uint32_t done_seq)
 {
     __shared__ __align__(16) uint32_t lds[Layout<PL, true>::words];  // the larger of the two directions
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), per_group = blockDim.x >> 6;
+    const Claims enc_claims = claims_of(n_enc, lp, enc_groups * per_group);
+    const Claims dec_claims = claims_of(n_dec, lp, (gridDim.x - enc_groups) * per_group);
     bool dec = blockIdx.x >= enc_groups;
+    // the wave's place among those that start on its list, and their number
+    const uint32_t place = (blockIdx.x - (dec ? enc_groups : 0u)) * per_group + wave;
+    const uint32_t step = (dec ? gridDim.x - enc_groups : enc_groups) * per_group;
     for (int pass = 0; pass < 2; ++pass, dec = !dec) {
-        if ((dec ? n_dec : n_enc) == 0)
+        const Claims claims = dec ? dec_claims : enc_claims;
+        if (claims.n == 0)
             continue;  // uniform across the grid: no tables to load, no barrier to meet
+        if (pass == 1) {
+            // Help with the other list only if its counter has claims left.
+            // The tables are done with, so one thread's look at the counter
+            // reaches the workgroup through their place.
+            if (claims.dealt == claims.n)
+                break;
+            if (threadIdx.x == 0)
+                lds[0] = __hip_atomic_load(&counters[dec ? 1 : 0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const uint32_t claimed = lds[0];
+            __syncthreads();  // read by all before the fill writes it
+            if (claimed >= claims.n - claims.dealt)
+                break;
+        }
+        const uint32_t first_claim = pass == 0 ? place : claims.dealt;
         if (dec)
             fill_tables<PL, true>(lds, &c_tables);
         else
             fill_tables<PL, false>(lds, &c_tables);
         __syncthreads();
         if (dec)
-            drain<true, BPT, PL>(items, n_enc, n_dec, key_table, n_slots, in_base, out_base, in_blocks, out_blocks,
-                             counters, lds);
+            drain<true, BPT, PL>(items, n_enc, lp, claims, first_claim, step, key_table, n_slots, in_base, out_base,
+                                 in_blocks, out_blocks, counters, lds);
         else
-            drain<false, BPT, PL>(items, 0, n_enc, key_table, n_slots, in_base, out_base, in_blocks, out_blocks,
-                              counters, lds);
+            drain<false, BPT, PL>(items, 0, lp, claims, first_claim, step, key_table, n_slots, in_base, out_base,
+                                  in_blocks, out_blocks, counters, lds);
         __syncthreads();  // every wave is done with these tables before LDS is refilled
     }
     if (threadIdx.x == 0) {
-        __threadfence();
+        // Only the completion word needs the outputs released before the
+        // launch ends: a fence writes the XCD's L2 back, about 1 us in turn
+        // for each of the 32 workgroups on it.
+        if (done_word != nullptr)
+            __threadfence();
         if (atomicAdd(&counters[2], 1u) == gridDim.x - 1) {
             atomicExch(&counters[0], 0u);
             atomicExch(&counters[1], 0u);
             atomicExch(&counters[2], 0u);
-            __threadfence();
             // every workgroup released its stores before counting itself
-            if (done_word != nullptr)
+            if (done_word != nullptr) {
+                __threadfence();
                 __hip_atomic_store(done_word, done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
         }
     }
 }
@@ -248,7 +337,7 @@ hipError_t launch_batch_impl(const BatchArgs& a, int bpt, int placement, int gri
 #define AESGPU_BATCH_LAUNCH(B, P)                                                                                  \
     hipLaunchKernelGGL((batch_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, a.n_enc, a.n_dec,           \
                        a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base), static_cast<uint4*>(a.out_base), \
-                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, done_word, seq)
+                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, a.parts_log2, done_word, seq)
 #define AESGPU_BATCH_PLACEMENT(P)                   \
     switch (bpt) {                                  \
     case 1: AESGPU_BATCH_LAUNCH(1, P); break;       \

@@ -182,3 +182,28 @@ def test_batch_config_2_full_mix(oracle_lib):
             src = in_arena[lo + a:lo + z].cpu().numpy()
             want = oracle_lib.ecb_decrypt(keys[i], src) if mix.decrypt[i] else oracle_lib.ecb_encrypt(keys[i], src)
             assert np.array_equal(out_arena[lo + a:lo + z].cpu().numpy(), want), (int(i), a)
+
+
+@pytest.mark.parametrize("n,hi_bytes,chunk,wg,grid", [
+    (1, 4096, 2048, 1024, 0), (2, 300 << 10, 1 << 24, 1024, 0), (7, 40 << 10, 64, 1024, 0),
+    (130, 8192, 100, 1024, 0), (2100, 1024, 2048, 1024, 0), (300, 8192, 64, 64, 2), (257, 16 << 10, 65, 128, 3)])
+def test_items_in_parts_and_claims_several_at_a_time(oracle_lib, n, hi_bytes, chunk, wg, grid):
+    """Lists short enough to be walked in 32 ... 1 parts per item (items of one
+    block, of odd lengths, of the whole message) and lists so long for their
+    grid that the counters hand out several claims at once; one item whose key
+    slot is out of range is counted once; the second launch finds the counters
+    as the first left them."""
+    torch = cuda()
+    mix, keys, x, b = build(900 + n, n, hi_bytes, chunk, aes.BatchConfig(bpt=4, wg=wg, grid=grid))
+    items = b.items_dev.cpu().numpy().view(aes.ITEM_DTYPE).copy()
+    bad = np.zeros(1, dtype=aes.ITEM_DTYPE)
+    bad["nblocks"], bad["key_slot"] = 3, n
+    b.items_dev = torch.from_numpy(np.concatenate([items, bad]).view(np.uint8).copy()).cuda()
+    b.n_dec += 1
+    for launch in (1, 2):
+        b.out_arena.zero_()
+        b.launch()
+        torch.cuda.synchronize()
+        assert b.rejected_items() == launch
+        assert not b.counters_dev[:3].any()
+        check_against_oracle(oracle_lib, mix, keys, x, b.out_arena.cpu().numpy())
