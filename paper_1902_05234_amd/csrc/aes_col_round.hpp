@@ -12,8 +12,28 @@
 #include <cstdint>
 
 #include "aes_device.hpp"
+#include "aes_internal.hpp"
 
 namespace aesgpu {
+
+// Workgroups of a launch of kern, one column word per lane, over nblocks:
+// shape.grid if set, else persistent (as many as fit on every CU at once,
+// given LDS and registers), never more than the blocks can keep busy.
+inline hipError_t col_grid_for(const void* kern, const LaunchShape& shape, int cus, uint64_t nblocks, int* grid_out)
+{
+    int grid = shape.grid;
+    if (grid <= 0) {
+        int per_cu = 0;
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, shape.wg, 0);
+        if (e != hipSuccess)
+            return e;
+        grid = cus * (per_cu > 0 ? per_cu : 1);
+    }
+    const uint64_t per_group = (uint64_t)shape.wg / 4u;  // blocks per workgroup at a time
+    const uint64_t needed = (nblocks + per_group - 1) / per_group;
+    *grid_out = (uint64_t)grid > needed ? (int)needed : grid;
+    return hipSuccess;
+}
 
 // Word of quad lane (lane + D) mod 4, D = 1..3, by a DPP quad permutation.
 template <int D>

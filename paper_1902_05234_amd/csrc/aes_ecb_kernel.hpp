@@ -77,11 +77,10 @@ __global__ __launch_bounds__(1024) void ecb_kernel(const uint4* __restrict__ in,
     }
 }
 
-// Workgroups of a launch of kern over nblocks, per_group blocks to each at a
-// time: shape.grid if set, else persistent (as many as fit on every CU at
-// once, given LDS and registers), never more than the blocks can keep busy.
-inline hipError_t grid_for(const void* kern, const LaunchShape& shape, int cus, uint64_t nblocks, uint64_t per_group,
-                           int* grid_out)
+// Workgroups of a launch of kern over nblocks: shape.grid if set, else
+// persistent (as many as fit on every CU at once, given LDS and registers),
+// never more than the blocks can keep busy.
+inline hipError_t grid_for(const void* kern, const LaunchShape& shape, int cus, uint64_t nblocks, int* grid_out)
 {
     int grid = shape.grid;
     if (grid <= 0) {
@@ -91,22 +90,12 @@ inline hipError_t grid_for(const void* kern, const LaunchShape& shape, int cus, 
             return e;
         grid = cus * (per_cu > 0 ? per_cu : 1);
     }
+    const uint64_t per_group = (uint64_t)shape.wg * shape.bpt;
     const uint64_t needed = (nblocks + per_group - 1) / per_group;
     if ((uint64_t)grid > needed)
         grid = (int)needed;
     *grid_out = grid;
     return hipSuccess;
-}
-
-inline hipError_t grid_for(const void* kern, const LaunchShape& shape, int cus, uint64_t nblocks, int* grid_out)
-{
-    return grid_for(kern, shape, cus, nblocks, (uint64_t)shape.wg * shape.bpt, grid_out);
-}
-
-// One column word per lane: a quarter block per thread.
-inline hipError_t col_grid_for(const void* kern, const LaunchShape& shape, int cus, uint64_t nblocks, int* grid_out)
-{
-    return grid_for(kern, shape, cus, nblocks, (uint64_t)shape.wg / 4u, grid_out);
 }
 
 template <int NR, bool kDecrypt, int BPT, int PL>
