@@ -239,10 +239,10 @@ int aes_cbc_encrypt_msgs_variant(const uint32_t *rk, int nr, const aes_cbc_msg *
  *   aes_cbc_encrypt_msgs; a message may run in place (equal ranges in one
  *   arena).  For one long message aes_cbc_decrypt is the faster call (every
  *   block of it in parallel); this call is for many messages at once.
- * The default walks the set block by block, 64 blocks of consecutive
- * messages per wave at a time, so that lengths may vary freely; between
- * separate arenas several waves share the messages, so a few long ones also
- * fill the device.  In one arena no message is split over waves.
+ * The default walks the set block by block, 64 blocks per wave at a time of
+ * messages from all over the list, so that lengths may vary freely and in any
+ * order; between separate arenas several waves share the messages, so a few
+ * long ones also fill the device.  In one arena no message is split over waves.
  * The _variant form runs one of two other kernels: one message per lane (bpt
  * = blocks a lane decrypts at once: 1, 2 or 4), or one wave per message
  * (bpt = AES_BPT_WAVE_MSG + 1 or 2 blocks per lane per 64-block unit), with

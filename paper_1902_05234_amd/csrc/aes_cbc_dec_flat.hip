@@ -3,15 +3,22 @@
 //
 // Decryption has no chain (section 3.1.2, eq 2: P_i = invcipher(C_i) XOR
 // C_{i-1}), so any 64 blocks of a message set can be a wave's work.  A wave
-// takes a group of up to 64 consecutive messages, one record per lane, drops
-// the empty and the refused ones, and numbers the group's blocks from 0 by a
-// prefix sum over the lengths.  It then walks those numbers 64 at a time, one
-// block per lane, so every lane has a block however short or ragged the
-// messages are.  Which message a lane's block belongs to follows from one
-// 64-bit mask per step, the bit of every number at which a message starts:
-// the count of bits up to the lane gives the message, a lane permute its
-// offsets.  The block before a message's first one is its IV, read from the
-// record.
+// takes a group of up to 64 messages, one record per lane, drops the empty and
+// the refused ones, and numbers the group's blocks from 0 by a prefix sum over
+// the lengths.  It then walks those numbers 64 at a time, one block per lane,
+// so every lane has a block however short or ragged the messages are.  Which
+// message a lane's block belongs to follows from one 64-bit mask per step, the
+// bit of every number at which a message starts: the count of bits up to the
+// lane gives the message, a lane permute its offsets.  The block before a
+// message's first one is its IV, read from the record.
+//
+// A group's messages come from all over the list (aes_cbc_flat_split.hpp), so
+// that a list sorted by length, or one with its long messages in a row, keeps
+// all waves busy equally long.  With 64 consecutive messages to a group such
+// lists took (AES-128, us; consecutive -> spread; one wave per message between
+// them): 2^16 of 1 ... 4096 blocks sorted 2516 -> 415 (483), 2^14 of 1 ... 65536
+// sorted 9975 -> 1288 (2942), 2^16 with 64 of 65536 blocks in a row 22476 -> 644
+// (2550), 2^16 of 0 ... 256 sorted 175 -> 102 (115); in random order 104 -> 103.
 //
 // Short lists of long messages split the other way: `slices` waves share a
 // group (then one message) and take every slices-th step of it.  Block b
@@ -20,6 +27,7 @@
 // them, ahead of the stores of the step before, so in place is safe.
 #include <algorithm>
 
+#include "aes_cbc_flat_split.hpp"
 #include "aes_cbc_msgs.hpp"
 #include "aes_ecb_kernel.hpp"
 
@@ -68,9 +76,9 @@ __device__ __forceinline__ uint64_t push(uint32_t to, uint64_t v)
 
 template <int NR, int PL>
 __global__ __launch_bounds__(1024) void cbc_dec_flat_kernel(const FlatMsg* __restrict__ msgs, uint64_t nmsgs,
-                                                            uint32_t per_group, uint32_t slices, const uint4* in,
-                                                            uint64_t in_blocks, uint4* out, uint64_t out_blocks,
-                                                            uint32_t* rejected, RoundKeys rk)
+                                                            FlatSplit split, const uint4* in, uint64_t in_blocks,
+                                                            uint4* out, uint64_t out_blocks, uint32_t* rejected,
+                                                            RoundKeys rk)
 {
     __shared__ __align__(16) uint32_t lds[Layout<PL, true>::words];
     fill_tables<PL, true>(lds, &c_tables);
@@ -80,7 +88,8 @@ __global__ __launch_bounds__(1024) void cbc_dec_flat_kernel(const FlatMsg* __res
 
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t groups = (nmsgs + per_group - 1) / per_group;
+    const uint64_t groups = split.groups;
+    const uint32_t per_group = split.per_group, slices = split.slices;
     const uint64_t step = (uint64_t)slices * 64u;
     const uint64_t units = groups * slices;  // below 2^32 where slices > 1
     // a workgroup's waves that walk units; the others only help with the tables
@@ -88,11 +97,13 @@ __global__ __launch_bounds__(1024) void cbc_dec_flat_kernel(const FlatMsg* __res
     for (uint64_t u = wave < walk ? blockIdx.x * walk + wave : units; u < units; u += gridDim.x * walk) {
         const uint64_t g = slices > 1 ? static_cast<uint32_t>(u) / slices : u;
         const uint32_t slice = static_cast<uint32_t>(u - g * slices);
-        const uint64_t m0 = g * per_group;
+        // 32 bits number the group's messages from m0 on
+        const uint64_t m0 = split.run_log2 == 6u ? g * per_group : 0;
+        const uint64_t m = flat_message(split, g, min(lane, per_group - 1u));
         // one record per lane; a lane without one, or with one that is refused, has no blocks
         uint64_t nb = 0, d_in = 0, d_out = 0;
-        if (lane < per_group && m0 + lane < nmsgs) {
-            const FlatMsg* d = msgs + m0 + lane;
+        if (lane < per_group && m < nmsgs) {
+            const FlatMsg* d = msgs + m;
             const uint64_t n = d->nblocks, ib = d->in_block, ob = d->out_block;
             if (d->reserved == 0 && ib <= in_blocks && n <= in_blocks - ib && ob <= out_blocks &&
                 n <= out_blocks - ob) {
@@ -111,7 +122,7 @@ __global__ __launch_bounds__(1024) void cbc_dec_flat_kernel(const FlatMsg* __res
         uint64_t start = end - nb;
         d_in -= start;
         d_out -= start;
-        uint32_t rec = lane;
+        uint32_t rec = static_cast<uint32_t>(m - m0);
         // messages with blocks move to lanes 0 .. have - 1, in order
         const uint64_t some = __ballot(nb != 0);
         const uint32_t have = static_cast<uint32_t>(__popcll(some));
@@ -180,15 +191,13 @@ __global__ __launch_bounds__(1024) void cbc_dec_flat_kernel(const FlatMsg* __res
 }
 
 template <int NR, int PL>
-hipError_t launch_flat(const FlatMsg* msgs, uint64_t nmsgs, uint32_t per_group, uint32_t slices, const void* in,
-                       uint64_t in_blocks, void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk,
-                       int wg, int max_grid, hipStream_t stream)
+hipError_t launch_flat(const FlatMsg* msgs, uint64_t nmsgs, const FlatSplit& split, const void* in, uint64_t in_blocks,
+                       void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, int wg, int max_grid,
+                       hipStream_t stream)
 {
-    const uint64_t units = (nmsgs + per_group - 1) / per_group * slices;
-    const uint64_t grid = std::min<uint64_t>((uint64_t)max_grid, units);
-    hipLaunchKernelGGL((cbc_dec_flat_kernel<NR, PL>), dim3((uint32_t)grid), dim3(wg), 0, stream, msgs, nmsgs,
-                       per_group, slices, static_cast<const uint4*>(in), in_blocks, static_cast<uint4*>(out),
-                       out_blocks, rejected, rk);
+    const uint64_t grid = std::min<uint64_t>((uint64_t)max_grid, split.groups * split.slices);
+    hipLaunchKernelGGL((cbc_dec_flat_kernel<NR, PL>), dim3((uint32_t)grid), dim3(wg), 0, stream, msgs, nmsgs, split,
+                       static_cast<const uint4*>(in), in_blocks, static_cast<uint4*>(out), out_blocks, rejected, rk);
     return hipGetLastError();
 }
 
@@ -200,42 +209,19 @@ hipError_t launch_cbc_dec_flat(int nr, const void* msgs, uint64_t nmsgs, const v
                                void* out, uint64_t out_blocks, uint32_t* rejected, const RoundKeys& rk, int cus,
                                hipStream_t stream)
 {
-    const uint64_t c = (uint64_t)cus, resident = 16u * c;
-    const uint64_t mean = std::max<uint64_t>(1, in_blocks / nmsgs);  // of the arena: the lengths are on the device
-    uint64_t per_group, slices = 1;
-    if (in != out) {
-        // Groups as near to 64 messages as fill the device, each shared by as
-        // many waves as that leaves, down to one step each: the waves of a
-        // group have equally many steps, whatever its messages' lengths.
-        slices = std::max<uint64_t>(1, 64u * resident / nmsgs);
-        per_group = slices > 1 ? (nmsgs * slices + resident - 1) / resident : 0;
-    }
-    if (slices == 1) {
-        // A wave per group: as many messages as give every resident wave one
-        // group, in as many rounds as groups of 64 need, and at least a step.
-        const uint64_t rounds = (nmsgs + 64u * resident - 1) / (64u * resident);
-        per_group = std::max((nmsgs + resident * rounds - 1) / (resident * rounds), (64u + mean - 1) / mean);
-    }
-    per_group = std::min<uint64_t>({per_group, 64u, nmsgs});
-    const uint64_t groups = (nmsgs + per_group - 1) / per_group;
-    if (slices > 1)
-        slices = std::min<uint64_t>(std::max<uint64_t>(1, mean * per_group / 64u),
-                                    std::max<uint64_t>(1, resident / groups));
+    const FlatSplit split = flat_split(nmsgs, in_blocks, in == out, cus);
     // At least 8 waves, which fill the tables in one memory round trip (16
     // messages of 4 blocks 13.4 -> 6.1 us per launch against one wave).
-    const uint64_t per_cu = (groups * slices + c - 1) / c;
+    const uint64_t c = (uint64_t)cus, per_cu = (split.groups * split.slices + c - 1) / c;
     const int wg = (int)std::min<uint64_t>(1024, std::max<uint64_t>(512, 64u * per_cu));
     const FlatMsg* m = static_cast<const FlatMsg*>(msgs);
     switch (nr) {
     case 10:
-        return launch_flat<10, kPlace4>(m, nmsgs, (uint32_t)per_group, (uint32_t)slices, in, in_blocks, out,
-                                        out_blocks, rejected, rk, wg, cus, stream);
+        return launch_flat<10, kPlace4>(m, nmsgs, split, in, in_blocks, out, out_blocks, rejected, rk, wg, cus, stream);
     case 12:
-        return launch_flat<12, kPlace4>(m, nmsgs, (uint32_t)per_group, (uint32_t)slices, in, in_blocks, out,
-                                        out_blocks, rejected, rk, wg, cus, stream);
+        return launch_flat<12, kPlace4>(m, nmsgs, split, in, in_blocks, out, out_blocks, rejected, rk, wg, cus, stream);
     case 14:
-        return launch_flat<14, kPlace4>(m, nmsgs, (uint32_t)per_group, (uint32_t)slices, in, in_blocks, out,
-                                        out_blocks, rejected, rk, wg, cus, stream);
+        return launch_flat<14, kPlace4>(m, nmsgs, split, in, in_blocks, out, out_blocks, rejected, rk, wg, cus, stream);
     default: return hipErrorInvalidValue;
     }
 }
