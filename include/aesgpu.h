@@ -248,7 +248,8 @@ int aes_cbc_encrypt_msgs_variant(const uint32_t *rk, int nr, const aes_cbc_msg *
  * (bpt = AES_BPT_WAVE_MSG + 1 or 2 blocks per lane per 64-block unit), with
  * the given wg, table placement (not bitsliced) and grid.  The default takes
  * the first for 2^17 messages or more of at most 4 blocks on average (on 256
- * CUs) and the second within one arena for messages of 64 blocks or more.
+ * CUs) and the second for messages of 64 blocks or more within one arena, or
+ * in a short list whose arena holds a whole multiple of 64 blocks for each.
  * Asynchronous on stream.
  */
 int aes_cbc_decrypt_msgs(const uint32_t *rk, int nr, const aes_cbc_msg *msgs_dev, size_t nmsgs, const void *in_base,

@@ -300,7 +300,7 @@ aes_variant cbc_msgs_default(size_t nmsgs, int cus)
 
 // Shape of aes_cbc_decrypt_msgs when the caller names none.  The kernel that
 // walks the set block by block (kCbcFlat, which splits the work itself) takes
-// all but two kinds of set (AES-128, other kernel -> this one):
+// all but three kinds of set (AES-128, other kernel -> this one):
 //   - many very short messages, at most 4 blocks of the arena each and half a
 //     wave of them or more for every wave the device holds: finding each
 //     block's message costs more than lanes idle at ragged ends (2^20
@@ -308,12 +308,22 @@ aes_variant cbc_msgs_default(size_t nmsgs, int cus)
 //     message per lane with 4 blocks at a time;
 //   - messages that fill a wave (64 blocks of the arena each) within one
 //     arena, where no message may be split over waves: one wave per message
-//     has less to do (4096 of up to 16 KiB 43 -> 44 us).
-// Those two take workgroups just large enough to give every CU as many waves.
+//     has less to do (4096 of up to 16 KiB 43 -> 44 us);
+//   - at least as many messages as resident waves, of exactly a whole number of
+//     steps of the arena each, as equal pages back to back have, and at most 8
+//     steps for a wave: with every lane of one wave per message busy, finding
+//     the blocks' messages only adds to a short walk (4096 x 64 blocks 7.5 ->
+//     8.6 us, 8192 x 64 10.2 -> 13.0, 8192 x 256 26.0 -> 28.8; at 8 steps it
+//     evens out, 32768 x 64 29.8 -> 29.4, 65536 x 64 54.5 -> 51.9).  Shorter
+//     messages in slots of that size pay for it (8192 of 0 ... 256 blocks 22.3
+//     -> 19.9, 16384 of 0 ... 16 in slots of 64 15.8 -> 8.0).
+// Those take workgroups just large enough to give every CU as many waves.
 aes_variant cbc_dec_msgs_default(size_t nmsgs, size_t in_blocks, bool one_arena, int cus)
 {
     const uint64_t c = cus > 0 ? (uint64_t)cus : 256u, mean = in_blocks / nmsgs;
-    const bool lanes = mean <= 4u && nmsgs >= 32u * 16u * c, wave = one_arena && mean >= 64u;
+    const bool lanes = mean <= 4u && nmsgs >= 32u * 16u * c;
+    const bool pages = nmsgs >= 16u * c && mean % 64u == 0 && in_blocks % nmsgs == 0 && in_blocks <= 8u * 64u * 16u * c;
+    const bool wave = mean >= 64u && (one_arena || pages);
     if (!lanes && !wave)
         return aes_variant{kCbcFlat, 0, AES_PLACEMENT_TTABLE4, 0};
     const uint64_t waves = wave ? nmsgs : (nmsgs + 63u) / 64u;

@@ -457,3 +457,35 @@ def test_encrypt_default_over_list_lengths(oracle_lib, n, max_blocks, keybits, o
     run(ks, recs, src_dev, out, rejected=rej)
     assert int(rej.item()) == bad.sum()
     assert first_mismatch(to_host(out), want) is None
+
+
+@pytest.mark.parametrize("n,slot,spare", [(4096, 64, 0), (4096, 64, 1), (4095, 64, 0), (4097, 128, 0), (4096, 512, 0),
+                                          (4096, 576, 0)])
+def test_decrypt_default_around_whole_step_slots(oracle_lib, n, slot, spare):
+    """The default decryption of messages in slots of whole steps, at the least
+    number of messages and the most steps that it takes one wave per message
+    for, one message or one arena block beside them, full slots among short
+    and empty ones; sampled messages against the oracle, untouched bytes kept."""
+    torch = cuda()
+    g = inputs.rng(13, n, slot)
+    key = inputs.random_key(910 + slot, 128)
+    ks = aes.aes_expand_key(key)
+    recs = np.zeros(n, dtype=aes.CBC_MSG_DTYPE)
+    nb = g.integers(0, slot + 1, n)
+    nb[g.random(n) < 0.5] = slot
+    recs["nblocks"] = nb
+    recs["in_block"] = np.arange(n) * slot
+    recs["out_block"] = g.permutation(n) * slot
+    recs["iv"] = g.integers(0, 256, (n, 16))
+    src = inputs.random_bytes(911 + slot, 16 * (n * slot + spare))
+    out = torch.full((16 * n * slot,), SENTINEL, dtype=torch.uint8, device="cuda")
+    run_dec(ks, recs, to_dev(src), out)
+    got = to_host(out).reshape(n, 16 * slot)
+    at = np.empty(n, dtype=np.int64)
+    at[recs["out_block"].astype(np.int64) // slot] = np.arange(n)  # the message in each output slot
+    used = np.arange(16 * slot)[None, :] < 16 * nb[at][:, None]
+    assert (got[~used] == SENTINEL).all()
+    for m in [0, 1, n - 1, *g.integers(0, n, 60)]:
+        a, size = 16 * slot * int(m), 16 * int(nb[m])
+        want = oracle_lib.cbc_decrypt(key, recs[m]["iv"].tobytes(), src[a:a + size]) if size else src[:0]
+        assert first_mismatch(got[int(recs["out_block"][m]) // slot][:size], want) is None, int(m)
