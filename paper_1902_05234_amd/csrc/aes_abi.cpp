@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "../../include/aesgpu.h"
+#include "aes_batch_claims.hpp"
 #include "aes_cbc_msgs.hpp"
 #include "aes_internal.hpp"
 #include "aes_tables.hpp"
@@ -474,7 +475,8 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
     }
     out->args = BatchArgs{reinterpret_cast<const WorkItem*>(items_dev), (uint32_t)n_enc, (uint32_t)n_dec,
                           key_table_dev, (uint32_t)n_slots, in_base, out_base, (uint64_t)in_blocks,
-                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, lp};
+                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, lp,
+                          claims_worth(in_blocks, (uint64_t)n_enc + n_dec)};
     out->bpt = c.bpt;
     out->wg = c.wg;
     out->grid = grid;

@@ -32,6 +32,7 @@
 #include <cstdint>
 #include <mutex>
 
+#include "aes_batch_claims.hpp"
 #include "aes_batch_signal.hpp"
 #include "aes_device.hpp"
 #include "aes_internal.hpp"
@@ -85,43 +86,10 @@ __device__ __forceinline__ void run_item(const uint4* __restrict__ in, uint4* __
     }
 }
 
-// How the claims of one list are dealt: 2^lp parts of each item, `waves` waves
-// that start on the list.  The first `dealt` claims go to those waves in turn,
-// the rest to whichever wave asks, through the list's counter.  An update of
-// the counter takes about 14 ns in which no other is served: 1000 items of one
-// unit on 1008 waves took 43 us, the time of their 3000 updates.  So a list
-// that one claim per wave covers is dealt whole, a longer one to five eighths
-// but at most 8 per wave: dealt waves drift apart over the arenas (20,000
-// messages of up to 8 MiB, 104 claims per wave: 9448 us claimed one by one,
-// 9310 so, 9786 with five eighths dealt), and what is left evens out their
-// sums over items of different lengths.
-struct Claims {
-    uint32_t n, dealt;
-};
-
-__device__ __forceinline__ Claims claims_of(uint32_t n_items, uint32_t lp, uint32_t waves)
-{
-    const uint32_t n = n_items << lp;
-    if (n <= waves)
-        return Claims{n, n};
-    const uint32_t rounds = waves != 0 ? n / waves : 0u;
-    return Claims{n, min((rounds % 16u * 5u + 7u) / 8u + rounds / 16u * 8u, 8u) * waves};
-}
-
-// Claims taken with one update of the counter when `left` are left: several
-// while many are, and twice as many as the last time, up to eight times the
-// number for long items, where none of those was over one row of blocks
-// (100,000 messages of up to 1 KiB: 1233 us one by one, 801 with the number
-// for long items, 280 so).
-__device__ __forceinline__ uint32_t claims_at_once(uint32_t left, uint32_t waves, uint32_t taken, uint32_t longest)
-{
-    const uint32_t few = 1u + left / 16u / waves;
-    return longest <= 64u ? max(few, min(2u * taken, 1u + left / 2u / waves)) : few;
-}
-
 template <bool kDecrypt, int BPT, int PL>
 __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32_t first_item, uint32_t lp,
                                       const Claims& claims, uint32_t first_claim, uint32_t claim_step,
+                                      uint32_t left, uint32_t waves, uint32_t worth,
                                       const uint32_t* __restrict__ key_table, uint32_t n_slots,
                                       const uint4* __restrict__ in_base, uint4* __restrict__ out_base,
                                       uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
@@ -131,7 +99,7 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
     const LaneBases<PL, kDecrypt> lb(threadIdx.x);
     uint32_t dealt = first_claim;  // the wave's next claim among the dealt ones
     uint32_t next = 0, run = 0, taken = 1, longest = 0;
-    uint32_t left = claims.n - claims.dealt;  // as the wave last saw it
+    // left: claims that the counter has left, as the wave last saw it
     uint32_t* const counter = &counters[kDecrypt ? 1 : 0];
     for (;;) {
         uint32_t idx = dealt;
@@ -139,7 +107,7 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
             dealt += claim_step;
         } else if (claims.dealt < claims.n) {
             if (run == 0) {
-                run = taken = claims_at_once(left, claim_step, taken, longest);
+                run = taken = claims_at_once(left, waves, taken, longest, worth);
                 longest = 0;
                 if (lane == 0)
                     next = claims.dealt + atomicAdd(counter, run);
@@ -191,18 +159,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPla
                                                      uint32_t n_slots, const uint4* __restrict__ in_base,
                                                      uint4* __restrict__ out_base, uint64_t in_blocks,
                                                      uint64_t out_blocks, uint32_t* counters, uint32_t enc_groups,
-                                                     uint32_t lp, uint32_t* done_word, uint32_t done_seq)
+                                                     uint32_t lp, uint32_t worth, uint32_t* done_word, uint32_t done_seq)
 {
     __shared__ __align__(16) uint32_t lds[Layout<PL, true>::words];  // the larger of the two directions
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), per_group = blockDim.x >> 6;
-    const Claims enc_claims = claims_of(n_enc, lp, enc_groups * per_group);
-    const Claims dec_claims = claims_of(n_dec, lp, (gridDim.x - enc_groups) * per_group);
+    const Claims enc_claims = claims_of(n_enc, lp, enc_groups * per_group, worth);
+    const Claims dec_claims = claims_of(n_dec, lp, (gridDim.x - enc_groups) * per_group, worth);
     bool dec = blockIdx.x >= enc_groups;
     // the wave's place among those that start on its list, and their number
     const uint32_t place = (blockIdx.x - (dec ? enc_groups : 0u)) * per_group + wave;
     const uint32_t step = (dec ? gridDim.x - enc_groups : enc_groups) * per_group;
     for (int pass = 0; pass < 2; ++pass, dec = !dec) {
         const Claims claims = dec ? dec_claims : enc_claims;
+        uint32_t left = claims.n - claims.dealt;
         if (claims.n == 0)
             continue;  // uniform across the grid: no tables to load, no barrier to meet
         if (pass == 1) {
@@ -216,21 +185,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPla
             __syncthreads();
             const uint32_t claimed = lds[0];
             __syncthreads();  // read by all before the fill writes it
-            if (claimed >= claims.n - claims.dealt)
+            if (claimed >= left)
                 break;
+            left -= claimed;
         }
         const uint32_t first_claim = pass == 0 ? place : claims.dealt;
+        const uint32_t own = (dec ? gridDim.x - enc_groups : enc_groups) * per_group;
+        const uint32_t waves = claim_waves(own, gridDim.x * per_group);
         if (dec)
             fill_tables<PL, true>(lds, &c_tables);
         else
             fill_tables<PL, false>(lds, &c_tables);
         __syncthreads();
         if (dec)
-            drain<true, BPT, PL>(items, n_enc, lp, claims, first_claim, step, key_table, n_slots, in_base, out_base,
-                                 in_blocks, out_blocks, counters, lds);
+            drain<true, BPT, PL>(items, n_enc, lp, claims, first_claim, step, left, waves, worth, key_table, n_slots,
+                                 in_base, out_base, in_blocks, out_blocks, counters, lds);
         else
-            drain<false, BPT, PL>(items, 0, lp, claims, first_claim, step, key_table, n_slots, in_base, out_base,
-                                  in_blocks, out_blocks, counters, lds);
+            drain<false, BPT, PL>(items, 0, lp, claims, first_claim, step, left, waves, worth, key_table, n_slots,
+                                  in_base, out_base, in_blocks, out_blocks, counters, lds);
         __syncthreads();  // every wave is done with these tables before LDS is refilled
     }
     if (threadIdx.x == 0) {
@@ -337,7 +309,8 @@ hipError_t launch_batch_impl(const BatchArgs& a, int bpt, int placement, int gri
 #define AESGPU_BATCH_LAUNCH(B, P)                                                                                  \
     hipLaunchKernelGGL((batch_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, a.n_enc, a.n_dec,           \
                        a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base), static_cast<uint4*>(a.out_base), \
-                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, a.parts_log2, done_word, seq)
+                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, a.parts_log2, a.claims_worth, \
+                       done_word, seq)
 #define AESGPU_BATCH_PLACEMENT(P)                   \
     switch (bpt) {                                  \
     case 1: AESGPU_BATCH_LAUNCH(1, P); break;       \

@@ -1,0 +1,64 @@
+// aes_batch_claims.hpp -- how the batched launch (aes_batch.hip) hands out the
+// claims of a work list.  Plain arithmetic, shared by the kernel and a host
+// test that plays lists through it.
+#pragma once
+#include <cstdint>
+
+namespace aesgpu {
+
+// Most claims worth taking with one update of a list's counter, for n claims
+// over `blocks` blocks in all: as many as hold the 1200 blocks that the device
+// walks (at 1330 GB/s) in the 14 ns of an update.  Longer items cost nothing
+// one by one, and several in one wave's hands do: 20,000 messages of up to 8
+// MiB that are an item each 20.7 ms one by one, 25.5 in runs.
+constexpr uint32_t claims_worth(uint64_t blocks, uint64_t n)
+{
+    const uint64_t mean = n != 0 ? blocks / n : 0;
+    return 1u + static_cast<uint32_t>(1200u / (mean != 0 ? mean : 1u));
+}
+
+// The claims of one list: 2^lp parts of each item, of which the first `dealt`
+// go to the `waves` waves that start on the list, in turn, and the rest to
+// whichever wave asks, through the list's counter.  An update of the counter
+// takes about 14 ns in which no other is served: 1000 items of one unit on 1008
+// waves took 43 us, the time of their 3000 updates.  So a list that one claim
+// per wave covers is dealt whole, of a longer one every wave gets five eighths
+// of its share, rounded up, at most 8 and no more than is worth an update:
+// dealt claims stay with their wave, and dealt waves drift apart over the
+// arenas (20,000 messages of up to 8 MiB in items of 2048 blocks, 94 claims per
+// wave: 9.65 ms one by one, 10.2 with eight dealt, 9.5 with one).
+struct Claims {
+    uint32_t n, dealt;
+};
+
+constexpr Claims claims_of(uint32_t n_items, uint32_t lp, uint32_t waves, uint32_t worth)
+{
+    const uint32_t n = n_items << lp;
+    if (n <= waves || waves == 0)
+        return Claims{n, waves == 0 ? 0u : n};
+    const uint32_t share = n / waves, part = share < 13u ? (share * 5u + 7u) / 8u : 8u;
+    return Claims{n, (part < worth ? part : worth) * waves};
+}
+
+// Waves that a list's claims are to last for: those that start on it, or half
+// of the launch where these are fewer, because the others come over once
+// their own list is dry.  (With the starting waves of a wave's own list for
+// both, 10 encryption and 50,000 decryption items of 256 blocks left 17,360
+// claims to sixteen helping waves in runs of 68: 672 us one by one, 950 so, 222
+// now.)
+constexpr uint32_t claim_waves(uint32_t own, uint32_t all) { return own > all / 2u ? own : (all + 1u) / 2u; }
+
+// Claims taken with one update of the counter when `left` are left for `waves`
+// waves: a sixteenth of a wave's share and one, and twice as many as the last
+// time, up to two fifths of the share, where none of those was over 512 blocks
+// (100,000 messages of up to 1 KiB 1234 us one by one, 299 so; of up to 8 KiB
+// 1236 -> 327; half the share: 282 and 310, but its last runs end unevenly).
+constexpr uint32_t claims_at_once(uint32_t left, uint32_t waves, uint32_t taken, uint32_t longest, uint32_t worth)
+{
+    const uint32_t few = 1u + left / 16u / waves, most = 1u + (left / waves + 1u) * 2u / 5u;
+    const uint32_t more = longest > 512u ? few : 2u * taken < most ? 2u * taken : most;
+    const uint32_t n = few > more ? few : more;
+    return n < worth ? n : worth;
+}
+
+}  // namespace aesgpu

@@ -92,6 +92,7 @@ struct BatchArgs {
     // blocks), so that several waves share one; 0: an item by one wave.  The
     // claims, (n_enc or n_dec) << parts_log2, fit 31 bits where it is not 0.
     uint32_t parts_log2 = 0;
+    uint32_t claims_worth = 1;  // most claims taken with one update of a counter (aes_batch_claims.hpp)
 };
 
 // placement: kPlace4 / kPlace2 / kPlace1 (the table placements of the plain kernel)

@@ -207,3 +207,29 @@ def test_items_in_parts_and_claims_several_at_a_time(oracle_lib, n, hi_bytes, ch
         assert b.rejected_items() == launch
         assert not b.counters_dev[:3].any()
         check_against_oracle(oracle_lib, mix, keys, x, b.out_arena.cpu().numpy())
+
+
+@pytest.mark.parametrize("few,many,hi_bytes,chunk,wg,grid", [
+    (3, 3000, 4096, 64, 1024, 0), (40, 2500, 512, 2048, 64, 40), (1, 700, 16 << 10, 100, 128, 4)])
+@pytest.mark.parametrize("few_decrypt", [False, True])
+def test_lists_of_very_unequal_size(oracle_lib, few, many, hi_bytes, chunk, wg, grid, few_decrypt):
+    """A handful of items in one direction beside thousands in the other, so
+    that most claims of the long list are taken by waves that started on the
+    short one and by counter updates worth several claims."""
+    torch = cuda()
+    n = few + many
+    mix = inputs.message_mix(1700 + n, n, hi_bytes=hi_bytes)
+    mix.decrypt[:] = np.arange(n) % (n // few) == 1
+    if not few_decrypt:
+        mix.decrypt[:] = ~mix.decrypt
+    keys = [inputs.random_key(int(s), int(b)) for s, b in zip(mix.key_seed, mix.keybits)]
+    x = inputs.random_bytes(1700 + n, 16 * mix.total_blocks)
+    in_arena = torch.from_numpy(x).cuda()
+    b = batch.prepare(batch.messages_from_mix(mix), batch.key_table(keys), in_arena, torch.zeros_like(in_arena),
+                      chunk_blocks=chunk, cfg=aes.BatchConfig(bpt=2, wg=wg, grid=grid))
+    for _ in range(2):
+        b.out_arena.zero_()
+        b.launch()
+        torch.cuda.synchronize()
+        assert b.rejected_items() == 0 and not b.counters_dev[:3].any()
+        check_against_oracle(oracle_lib, mix, keys, x, b.out_arena.cpu().numpy())
