@@ -122,3 +122,16 @@ def test_helpers_take_no_more_than_their_share(lib):
         longest = -(-max(int(x.max()) for x in lists) // 64)
         # a wave's last claims may hold a sixteenth of its share more than the others'
         assert play(lists, groups, 16, lib) <= 1.1 * alone + longest, name
+
+
+def test_idle_waves_of_one_direction_find_claims_of_the_other(lib):
+    """Workgroups split by item count, items of one direction long and of the
+    other one block: with every wave's first claim dealt the long list still
+    has claims for the waves that are through with the short one."""
+    waves = 16 * 16
+    for per_wave in (2, 3, 4, 5, 7, 10, 16, 40):
+        n = per_wave * waves // 2
+        lists = (np.full(n, 2048), np.ones(n, dtype=int))
+        for pair in (lists, lists[::-1]):
+            # as many rows more as the short list's items take
+            assert play(pair, (8, 8), 16, lib) <= 1.1 * play(pair, (8, 8), 16) + per_wave, per_wave
