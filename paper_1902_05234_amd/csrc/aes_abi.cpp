@@ -396,6 +396,20 @@ int run_cbc_msgs(bool decrypt, const uint32_t* rk, int nr, const aes_cbc_msg* ms
     return AES_OK;
 }
 
+// Workgroups of the configured variant that fit on every CU at once.
+int batch_resident_groups(const aes_batch_config& c, int* out)
+{
+    int cus = device_cu_count();
+    if (cus <= 0)
+        return fail(AES_EHIP, "cannot query the current HIP device");
+    int per_cu = 0;
+    hipError_t e = batch_groups_per_cu(c.bpt, c.placement, c.wg, &per_cu);
+    if (e != hipSuccess)
+        return fail_hip(e, "batch kernel occupancy query");
+    *out = cus * per_cu;
+    return AES_OK;
+}
+
 // Workgroups of a batch launch at most: cfg.grid, or as many as fit on every
 // CU at once for the configured variant.
 int batch_max_grid(const aes_batch_config& c, int* out)
@@ -413,15 +427,7 @@ int batch_max_grid(const aes_batch_config& c, int* out)
         *out = c.grid;
         return AES_OK;
     }
-    int cus = device_cu_count();
-    if (cus <= 0)
-        return fail(AES_EHIP, "cannot query the current HIP device");
-    int per_cu = 0;
-    hipError_t e = batch_groups_per_cu(c.bpt, c.placement, c.wg, &per_cu);
-    if (e != hipSuccess)
-        return fail_hip(e, "batch kernel occupancy query");
-    *out = cus * per_cu;
-    return AES_OK;
+    return batch_resident_groups(c, out);
 }
 
 // Arguments of one batch launch, checked; the caller supplies the counters.
@@ -459,23 +465,17 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
     int grid = 0, enc_groups = 0;
     // the item counts stand in for the byte shares (the items live on the device)
     batch_grid(n_enc, n_dec, n_enc, n_enc + n_dec, c.wg, max_grid, c.enc_groups, &grid, &enc_groups);
-    // Fewer items than the device holds waves: claimed in as many parts (up to
-    // 32) as leave every wave one claim at most, so that a short list spreads
-    // over all CUs and nothing goes through the claim counters.
-    const uint64_t per_group = (uint64_t)(c.wg / 64);
-    uint32_t lp = 0;
-    for (uint32_t p = 0; p <= 5u; ++p) {
-        const uint64_t need_e = (((uint64_t)n_enc << p) + per_group - 1) / per_group;
-        const uint64_t need_d = (((uint64_t)n_dec << p) + per_group - 1) / per_group;
-        if (need_e + need_d > (uint64_t)max_grid)
-            break;
-        lp = p;
-        grid = (int)(need_e + need_d);
-        enc_groups = (int)need_e;
+    int resident = max_grid;
+    if (c.grid > 0 && (rc = batch_resident_groups(c, &resident)) != AES_OK)
+        return rc;
+    const ShortList few = short_list(n_enc, n_dec, (uint32_t)(c.wg / 64), (uint64_t)max_grid, (uint64_t)resident);
+    if (few.grid != 0) {
+        grid = (int)few.grid;
+        enc_groups = (int)few.enc_groups;
     }
     out->args = BatchArgs{reinterpret_cast<const WorkItem*>(items_dev), (uint32_t)n_enc, (uint32_t)n_dec,
                           key_table_dev, (uint32_t)n_slots, in_base, out_base, (uint64_t)in_blocks,
-                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, lp,
+                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, few.parts_log2,
                           claims_worth(in_blocks, (uint64_t)n_enc + n_dec)};
     out->bpt = c.bpt;
     out->wg = c.wg;

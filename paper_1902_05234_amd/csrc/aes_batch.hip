@@ -5,8 +5,9 @@
 // items.  Each wave takes one item at a time (the first ones dealt out, the
 // rest claimed with an atomic counter), loads that item's round keys as
 // uniform values, and runs the same round core as the plain kernel for the
-// item's key size.  A list of fewer items than the device holds waves is
-// walked in parts of items, so that it spreads over all CUs.
+// item's key size.  A caller's list of fewer items than the device holds waves
+// is walked in parts of items, so that it spreads over all CUs; the serving
+// engine's batches, several at a time on the device, go item by item.
 // (Time per launch, 4 tables, items of 2048 blocks: 30 messages of up to 1 MiB
 // 83 -> 9.5 us, 1000 of up to 4 KiB 43 -> 9.7, 2000 of up to 8 MiB 1160 ->
 // 1115, against items claimed one by one, each by one wave.)

@@ -65,4 +65,29 @@ constexpr uint32_t claims_at_once(uint32_t left, uint32_t waves, uint32_t taken,
     return n < worth ? n : worth;
 }
 
+// Launch shape of lists that one claim per resident wave covers: every item in
+// as many parts (up to 32) as leave every wave one claim at most, so that a
+// short list spreads over all CUs and nothing goes through the claim counters.
+// max_grid: workgroups that the caller allows, resident: that the device holds
+// at once; a list that does not fit both gets grid 0.  The parts of all items
+// are no more than the resident waves.
+struct ShortList {
+    uint32_t parts_log2, grid, enc_groups;
+};
+
+constexpr ShortList short_list(uint64_t n_enc, uint64_t n_dec, uint32_t waves_per_group, uint64_t max_grid,
+                               uint64_t resident)
+{
+    const uint64_t room = max_grid < resident ? max_grid : resident;
+    ShortList s{0u, 0u, 0u};
+    for (uint32_t p = 0; p <= 5u; ++p) {
+        const uint64_t need_e = ((n_enc << p) + waves_per_group - 1) / waves_per_group;
+        const uint64_t need_d = ((n_dec << p) + waves_per_group - 1) / waves_per_group;
+        if (need_e + need_d > room)
+            break;
+        s = ShortList{p, static_cast<uint32_t>(need_e + need_d), static_cast<uint32_t>(need_e)};
+    }
+    return s;
+}
+
 }  // namespace aesgpu

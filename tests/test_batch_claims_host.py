@@ -25,6 +25,12 @@ extern "C" uint32_t at_once(uint32_t left, uint32_t waves, uint32_t taken, uint3
 {
     return aesgpu::claims_at_once(left, waves, taken, longest, worth);
 }
+extern "C" void short_list(uint64_t n_enc, uint64_t n_dec, uint32_t per_group, uint64_t max_grid, uint64_t resident,
+                           uint32_t* out)
+{
+    const aesgpu::ShortList s = aesgpu::short_list(n_enc, n_dec, per_group, max_grid, resident);
+    out[0] = s.parts_log2, out[1] = s.grid, out[2] = s.enc_groups;
+}
 """
 
 
@@ -135,3 +141,23 @@ def test_idle_waves_of_one_direction_find_claims_of_the_other(lib):
         for pair in (lists, lists[::-1]):
             # as many rows more as the short list's items take
             assert play(pair, (8, 8), 16, lib) <= 1.1 * play(pair, (8, 8), 16) + per_wave, per_wave
+
+
+@pytest.mark.parametrize("resident,per_group", [(256, 16), (512, 16), (4096, 1)])
+def test_short_lists_take_no_more_workgroups_than_are_resident(lib, resident, per_group):
+    """An explicit grid is a limit, not the device's size: parts of items are
+    made for the waves that the device holds, one claim each."""
+    out = (ctypes.c_uint32 * 3)()
+    u64 = ctypes.c_uint64
+    for n_enc, n_dec in ((1, 0), (0, 1), (7, 3), (500, 500), (0, 1000), (4000, 90), (4096, 0), (2048, 2049), (9000, 1)):
+        for max_grid in (1, 2, 63, 256, 4096, 2**31 - 1):
+            lib.short_list(u64(n_enc), u64(n_dec), per_group, u64(max_grid), u64(resident), out)
+            lp, grid, enc_groups = out
+            room = min(max_grid, resident)
+            need = -(-n_enc // per_group) + -(-n_dec // per_group)
+            assert (grid != 0) == (need <= room)
+            if grid:
+                assert grid <= room and lp <= 5
+                assert (n_enc << lp) <= enc_groups * per_group and (n_dec << lp) <= (grid - enc_groups) * per_group
+                more = -(-(n_enc << lp + 1) // per_group) + -(-(n_dec << lp + 1) // per_group)
+                assert lp == 5 or more > room
