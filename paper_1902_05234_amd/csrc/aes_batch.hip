@@ -134,9 +134,12 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
         const uint32_t* kp = key_table + (uint64_t)(ok ? slot : 0u) * kSlotWords;
         const int nr = ok ? (int)__builtin_amdgcn_readfirstlane(kp[kSlotNr]) : 0;
         const uint32_t* kd = kp + (kDecrypt ? 64 : 0);
-        // the part's blocks: an equal share, in wave rows of 64 blocks
-        const uint32_t share = lp == 0 ? nb : ((nb + (64u << lp) - 1u) >> (6u + lp)) << 6;
-        const uint32_t from = part * share;  // at most nb + 63 * 2^lp
+        // The part's blocks: an equal share, in wave rows of 64 blocks.  An item
+        // moved within one arena onto part of itself goes whole to its first
+        // part's wave, which reads every block before it writes there.
+        const bool onto_itself = in_base == out_base && in_b != out_b && in_b < out_b + nb && out_b < in_b + nb;
+        const uint32_t share = lp == 0 || onto_itself ? nb : ((nb + (64u << lp) - 1u) >> (6u + lp)) << 6;
+        const uint32_t from = part * share;  // below 2^30 for an item that is ok
         const uint32_t n = from < nb ? (nb - from < share ? nb - from : share) : 0u;
         const uint4* src = in_base + in_b + from;
         uint4* dst = out_base + out_b + from;

@@ -233,3 +233,27 @@ def test_lists_of_very_unequal_size(oracle_lib, few, many, hi_bytes, chunk, wg, 
         torch.cuda.synchronize()
         assert b.rejected_items() == 0 and not b.counters_dev[:3].any()
         check_against_oracle(oracle_lib, mix, keys, x, b.out_arena.cpu().numpy())
+
+
+@pytest.mark.parametrize("bpt", [1, 2, 4])
+@pytest.mark.parametrize("down", [1, 3, 64, 700])
+def test_item_moved_down_onto_itself(oracle_lib, bpt, down):
+    """A single item whose output starts a few blocks before its input in the
+    same arena: one wave walks it upwards, whatever the length of the list."""
+    torch = cuda()
+    key = inputs.random_key(60, 192)
+    n = 3001
+    x = inputs.random_bytes(61 + down, 16 * (n + down))
+    items = np.zeros(2, dtype=aes.ITEM_DTYPE)
+    items["in_block"], items["out_block"], items["nblocks"] = down, 0, n
+    for decrypt in (False, True):
+        arena = torch.from_numpy(x).cuda()
+        counters = torch.zeros(4, dtype=torch.int32, device="cuda")
+        aes.aes_ecb_batch(torch.from_numpy(items[:1].view(np.uint8).copy()).cuda(), int(not decrypt), int(decrypt),
+                          batch.key_table([key]), arena, arena, counters, aes.BatchConfig(bpt=bpt))
+        torch.cuda.synchronize()
+        want = oracle_lib.ecb_decrypt(key, x[16 * down:]) if decrypt else oracle_lib.ecb_encrypt(key, x[16 * down:])
+        got = arena.cpu().numpy()
+        assert first_mismatch(got[:16 * n], want) is None
+        assert np.array_equal(got[16 * n:], x[16 * n:])
+        assert int(counters[3].item()) == 0
