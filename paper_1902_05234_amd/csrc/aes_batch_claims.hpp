@@ -10,9 +10,13 @@ namespace aesgpu {
 // over `blocks` blocks in all: as many as hold the 1200 blocks that the device
 // walks (at 1330 GB/s) in the 14 ns of an update.  Longer items cost nothing
 // one by one, and several in one wave's hands do: 20,000 messages of up to 8
-// MiB that are an item each 20.7 ms one by one, 25.5 in runs.
+// MiB that are an item each 20.7 ms one by one, 25.5 in runs.  Lists near 2^32
+// claims go one by one: the counter passes the end of a list by at most the
+// last claims of every wave, and must not wrap.
 constexpr uint32_t claims_worth(uint64_t blocks, uint64_t n)
 {
+    if (n >> 31)
+        return 1u;
     const uint64_t mean = n != 0 ? blocks / n : 0;
     return 1u + static_cast<uint32_t>(1200u / (mean != 0 ? mean : 1u));
 }

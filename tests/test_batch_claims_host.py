@@ -161,3 +161,15 @@ def test_short_lists_take_no_more_workgroups_than_are_resident(lib, resident, pe
                 assert (n_enc << lp) <= enc_groups * per_group and (n_dec << lp) <= (grid - enc_groups) * per_group
                 more = -(-(n_enc << lp + 1) // per_group) + -(-(n_dec << lp + 1) // per_group)
                 assert lp == 5 or more > room
+
+
+def test_counter_does_not_wrap_where_single_claims_would_not(lib):
+    """Every wave's last update may pass the end of the list, with what the wave
+    thought was left at most the whole list."""
+    for waves in (1, 16, 4096, 16 * 1024):
+        for n in (1000, 2**20, 2**30, 2**31 - 1, 2**31, 3 * 2**30, 2**32 - 2**20, 2**32 - 1):
+            for blocks in (0, n, 100 * n):
+                worth = lib.claims_worth(blocks, n)
+                most = max(lib.at_once(n, waves, taken, longest, worth) for taken in (1, 2**20) for longest in (1, 10**6))
+                assert most <= worth
+                assert worth == 1 or n + waves * most < 2**32, (waves, n, blocks)
