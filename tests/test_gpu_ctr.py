@@ -166,3 +166,24 @@ def test_column_form_every_partial_word_and_unit(oracle_lib, keybits, placement)
         aes.aes_tune_set(ks.nr, False, 1, small)
     x = inputs.random_bytes(632, 2 * MiB - 5)  # the largest size of this form: waves walk several units
     assert_same(to_host(gpu_ctr(ks, iv, to_dev(x))), oracle_lib.ctr_crypt(key, iv, x), "2 MiB - 5")
+
+
+@pytest.mark.parametrize("bpt,placement", [(1, 0), (2, 1), (4, 2), (1, 1)])
+@pytest.mark.parametrize("keybits", [128, 192, 256])
+def test_around_one_whole_unit_per_wave(oracle_lib, bpt, placement, keybits):
+    """Four waves: up to one unit each, one block and one unit more, with
+    counters that start on a unit and inside one, and a partial last block."""
+    torch = cuda()
+    key = inputs.random_key(650 + bpt, keybits)
+    ks = aes.aes_expand_key(key)
+    span = 64 * bpt
+    for start in (0, 1, span - 1):
+        iv = ((7 << 40) - span + start).to_bytes(16, "big")
+        for n in (16 * 4 * span - 16, 16 * 4 * span, 16 * 4 * span + 1, 16 * 4 * span + 16, 16 * 5 * span - 3):
+            x = inputs.random_bytes(651 + n, n)
+            out = torch.full((n + 16,), 0xA5, dtype=torch.uint8, device="cuda")
+            aes.aes_ctr_crypt_variant(ks.rk_enc, ks.nr, iv, 0, to_dev(x), out,
+                                      aes.Variant(bpt=bpt, wg=128, placement=placement, grid=2), nbytes=n)
+            got = to_host(out)
+            assert first_mismatch(got[:n], oracle_lib.ctr_crypt(key, iv, x)) is None, (start, n)
+            assert (got[n:] == 0xA5).all()
