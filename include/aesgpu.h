@@ -141,8 +141,9 @@ int aes_size_bucket(size_t nblocks);
  *   nbytes:       any length; a partial last block uses the leading bytes
  *                 of its key-stream block.  0 is a no-op returning AES_OK.
  * The variant is the encryption entry of the tuning table for
- * ceil(nbytes/16) blocks, or up to 2 MiB one column word per lane where that
- * entry is a whole-state one.  Asynchronous on stream.
+ * ceil(nbytes/16) blocks; where that is still the compiled-in one and a
+ * whole-state one, one column word per lane up to 8 KiB per compute unit (2
+ * MiB on 256).  Asynchronous on stream.
  */
 int aes_ctr_crypt(const uint32_t *rk, int nr, const uint8_t *iv, uint64_t block_offset, const void *in, void *out,
                   size_t nbytes, void *stream);

@@ -486,17 +486,25 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
 
 }  // namespace
 
-// The tuned encryption variant for CTR.  Up to 2 MiB a whole-state wave has
-// one unit, for which its shared counter words do not pay, so one column per
-// lane (which has none) stays ahead longer than in ECB: AES-128 on 2 tables,
-// 512 threads, whole state -> column: 586 KiB 5.46 -> 4.20 us, 1.14 MiB 5.52
-// -> 4.63, 2 MiB 5.62 -> 5.26, but 4 MiB 6.76 -> 7.34.
+// The tuned encryption variant for CTR.  Up to 2 MiB (on 256 CUs) a whole-state
+// wave has one unit, for which its shared counter words do not pay, so one
+// column per lane (which has none) stays ahead longer than in ECB.  On 2
+// tables, 512 threads, whole state -> column, us: 1 MiB AES-128 5.23 -> 4.11,
+// AES-192 5.59 -> 4.37, AES-256 6.21 -> 4.37; 2 MiB 5.31 -> 5.13, 5.73 -> 5.40,
+// 6.28 -> 5.68; but 4 MiB 6.35 -> 7.20, 6.88 -> 7.72, 7.43 -> 8.19.  That holds
+// against the compiled-in entry of the size; one that aes_tune_set put in its
+// place is taken as it is.
 aes_variant ctr_variant(int nr, uint64_t nblocks)
 {
     aes_variant v;
     aes_tune_get(nr, 0, (size_t)nblocks, &v);
-    if (v.bpt != AES_BPT_COLUMN && nblocks <= 131072u)
-        return aes_variant{AES_BPT_COLUMN, 512, AES_PLACEMENT_TTABLE2, 0};
+    const TuneDefault& d = kTuneDefaults[nr_index(nr)][0][size_bucket(nblocks)];
+    const bool compiled_in = v.bpt == d.bpt && v.wg == d.wg && v.placement == d.placement;
+    if (compiled_in && v.bpt != AES_BPT_COLUMN) {
+        const int cus = device_cu_count();
+        if (nblocks <= 512u * (uint64_t)(cus > 0 ? cus : 256))
+            return aes_variant{AES_BPT_COLUMN, 512, AES_PLACEMENT_TTABLE2, 0};
+    }
     table_variant(&v);
     return v;
 }

@@ -5,6 +5,8 @@ covers every block exactly once; (2) the shared/lane split of rounds 1-2
 (the 27 lookups a unit shares, the 1 + 4 each lane does) gives the same
 key stream as the whole cipher, emulated in numpy with the library's
 T-table and checked against the CPU oracle's CTR."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -118,3 +120,32 @@ def test_shared_and_lane_lookups_give_the_cipher(oracle_lib, keybits, span):
         want = oracle_lib.ctr_crypt(key, c0.to_bytes(16, "big"), np.zeros(16 * n, dtype=np.uint8))
         got = cached_keystream(ks, c0, n, span)
         assert np.array_equal(got, want), hex(c0)
+
+
+def _ctr_variant(nr, nblocks):
+    """The library's choice for aes_ctr_crypt (an internal C++ function of the
+    shared library, by its linker name)."""
+    f = aes._lib()["_ZN6aesgpu11ctr_variantEim"]
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_uint64], aes._Variant
+    v = f(nr, nblocks)
+    return v.bpt, v.wg, v.placement
+
+
+@pytest.mark.parametrize("nr", [10, 12, 14])
+def test_installed_tuning_entry_steers_ctr(nr):
+    """aes_ctr_crypt departs from the tuning table only at the table's
+    compiled-in entries; an entry set in their place is taken."""
+    for nbytes in (16, 4096, 65536, 512 << 10, (512 << 10) + 16, 1 << 20, 2 << 20):
+        nblocks = nbytes // 16
+        old = aes.aes_tune_get(nr, False, nblocks)
+        assert _ctr_variant(nr, nblocks)[0] == aes.AES_BPT_COLUMN
+        try:
+            for bpt, wg, placement in ((1, 256, 0), (2, 1024, 2), (aes.AES_BPT_COLUMN, 64, 0)):
+                aes.aes_tune_set(nr, False, nblocks, aes.Variant(bpt, wg, placement))
+                assert _ctr_variant(nr, nblocks) == (bpt, wg, placement)
+            # bitsliced entries are ECB only: the 2-table kernel stands in
+            aes.aes_tune_set(nr, False, nblocks, aes.Variant(1, 256, aes.AES_PLACEMENT_BITSLICED))
+            assert _ctr_variant(nr, nblocks) == (2, 1024, aes.AES_PLACEMENT_TTABLE2)
+        finally:
+            aes.aes_tune_set(nr, False, nblocks, old)
+        assert _ctr_variant(nr, nblocks)[0] == aes.AES_BPT_COLUMN
