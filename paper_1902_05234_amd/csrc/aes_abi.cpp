@@ -17,6 +17,7 @@
 #include "../../include/aesgpu.h"
 #include "aes_batch_claims.hpp"
 #include "aes_cbc_msgs.hpp"
+#include "aes_ctr_variant.hpp"
 #include "aes_internal.hpp"
 #include "aes_tables.hpp"
 
@@ -484,6 +485,15 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
     return AES_OK;
 }
 
+// Encryption entry of the tuning table for nblocks; whether it is the
+// compiled-in one.
+bool ctr_entry(int nr, uint64_t nblocks, aes_variant* v)
+{
+    aes_tune_get(nr, 0, (size_t)nblocks, v);
+    const TuneDefault& d = kTuneDefaults[nr_index(nr)][0][size_bucket(nblocks)];
+    return v->bpt == d.bpt && v->wg == d.wg && v->placement == d.placement;
+}
+
 }  // namespace
 
 // The tuned encryption variant for CTR.  Up to 2 MiB (on 256 CUs) a whole-state
@@ -497,14 +507,20 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
 aes_variant ctr_variant(int nr, uint64_t nblocks)
 {
     aes_variant v;
-    aes_tune_get(nr, 0, (size_t)nblocks, &v);
-    const TuneDefault& d = kTuneDefaults[nr_index(nr)][0][size_bucket(nblocks)];
-    const bool compiled_in = v.bpt == d.bpt && v.wg == d.wg && v.placement == d.placement;
-    if (compiled_in && v.bpt != AES_BPT_COLUMN) {
+    if (ctr_entry(nr, nblocks, &v) && v.bpt != AES_BPT_COLUMN) {
         const int cus = device_cu_count();
         if (nblocks <= 512u * (uint64_t)(cus > 0 ? cus : 256))
             return aes_variant{AES_BPT_COLUMN, 512, AES_PLACEMENT_TTABLE2, 0};
     }
+    table_variant(&v);
+    return v;
+}
+
+aes_variant ctr_whole_state_variant(int nr, uint64_t nblocks)
+{
+    aes_variant v;
+    if (ctr_entry(nr, nblocks, &v) && v.bpt == AES_BPT_COLUMN)
+        v.bpt = 1;
     table_variant(&v);
     return v;
 }

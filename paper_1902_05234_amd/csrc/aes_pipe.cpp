@@ -43,6 +43,7 @@
 #include <vector>
 
 #include "../../include/aesgpu.h"
+#include "aes_ctr_variant.hpp"
 #include "aes_host_word.hpp"
 #include "aes_internal.hpp"
 
@@ -75,6 +76,25 @@ struct aes_pipe {
 };
 
 namespace aesgpu {
+
+constexpr uint64_t kDirectMax = 4ull << 20;       // largest buffer run on host memory
+constexpr uint64_t kStagedPiece = 256u << 10;     // smallest piece of a staged one, and
+constexpr uint64_t kStagedPieces = 4;             // how many there are at most
+
+// On host memory the column form of CTR moves a buffer faster than the
+// whole-state one (pinned, 1 MiB 49.7 -> 45.0 us), but where the calling thread
+// copies between pageable and staging memory meanwhile, the whole call takes
+// longer with it from 352 KiB a piece on: AES-128, whole state -> column, 1.2
+// MB 83.6 -> 82.4 us, 1.4 MB 91.5 -> 92.1, 2 MiB 124 -> 130, 3.67 MB 198 -> 210.
+// The largest pieces, 1 MiB, whose copies are slower by themselves, are faster
+// in columns again (4 MiB 274 -> 258).
+aes_variant ctr_piece_variant(int nr, uint64_t nbytes, bool beside_copies)
+{
+    const uint64_t nblocks = nbytes / 16u + (nbytes % 16u != 0);
+    return beside_copies && nbytes > (352u << 10) && nbytes < kDirectMax / kStagedPieces
+               ? ctr_whole_state_variant(nr, nblocks)
+               : ctr_variant(nr, nblocks);
+}
 
 // [p, p + n) lies inside one page-locked host allocation that the device maps
 // at the same address, so a kernel may read and write it.  A failed query
@@ -144,17 +164,17 @@ bool overlap_partial(const void* a, const void* b, uint64_t n)
     return x != y && x < y + n && y < x + n;
 }
 
-constexpr uint64_t kDirectMax = 4ull << 20;
 constexpr uint64_t kMinPiece = 1ull << 20;  // smallest piece a pipelined buffer is cut into
 
-// The kernel for the bytes [off, off + len) of the message, in -> out on stream.
+// The kernel for the bytes [off, off + len) of the message, in -> out on
+// stream; beside_copies as in ctr_piece_variant.
 hipError_t launch_piece(int op, int nr, const RoundKeys& keys, const Counter128& c0, uint64_t off, const void* in,
-                        void* out, uint64_t len, int cus, hipStream_t stream)
+                        void* out, uint64_t len, int cus, hipStream_t stream, bool beside_copies = false)
 {
     const uint64_t blocks = (len + 15u) / 16u;
     aes_variant v;
     if (op == AES_PIPE_CTR)
-        v = ctr_variant(nr, blocks);
+        v = ctr_piece_variant(nr, len, beside_copies);
     else
         aes_tune_get(nr, op == AES_PIPE_ECB_DECRYPT ? 1 : 0, blocks, &v);
     const LaunchShape shape{v.bpt, v.wg, 0};
@@ -172,9 +192,6 @@ hipError_t launch_piece(int op, int nr, const RoundKeys& keys, const Counter128&
 // bytes (at most kStagedPieces of them): each is copied into the staging,
 // run there, and copied out as soon as its completion word arrives, so the
 // CPU copies of one piece overlap the kernel of another.
-constexpr uint64_t kStagedPiece = 256u << 10;
-constexpr uint64_t kStagedPieces = 4;
-
 hipError_t run_staged_pieces(aes_pipe* p, Slot& s, int op, int nr, const RoundKeys& keys, const Counter128& c0,
                              const uint8_t* src, uint8_t* dst, uint64_t nbytes, int cus)
 {
@@ -193,7 +210,7 @@ hipError_t run_staged_pieces(aes_pipe* p, Slot& s, int op, int nr, const RoundKe
     for (uint64_t i = 0; i * plen < nbytes && e == hipSuccess; ++i) {
         const uint64_t off = i * plen, len = len_of(i);
         std::memcpy(s.pin + off, src + off, len);
-        e = launch_piece(op, nr, keys, c0, off, s.pin + off, s.pin + off, len, cus, s.stream);
+        e = launch_piece(op, nr, keys, c0, off, s.pin + off, s.pin + off, len, cus, s.stream, np > 1);
         if (e != hipSuccess)
             break;
         ++launched;  // in flight from here on: drained below if anything fails

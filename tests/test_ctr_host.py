@@ -149,3 +149,27 @@ def test_installed_tuning_entry_steers_ctr(nr):
         finally:
             aes.aes_tune_set(nr, False, nblocks, old)
         assert _ctr_variant(nr, nblocks)[0] == aes.AES_BPT_COLUMN
+
+
+@pytest.mark.parametrize("nr", [10, 12, 14])
+def test_staged_pieces_choose_a_form_by_size(nr):
+    """A piece of a pageable host buffer takes the whole-state form between 352
+    KiB and 1 MiB while other pieces are copied, and aes_ctr_crypt's choice
+    otherwise; an installed entry is taken in any case."""
+    f = aes._lib()["_ZN6aesgpu17ctr_piece_variantEimb"]
+    f.argtypes, f.restype = [ctypes.c_int, ctypes.c_uint64, ctypes.c_bool], aes._Variant
+    for n in (1, 262144, 352 << 10, (352 << 10) + 1, 512 << 10, (512 << 10) + 1, (1 << 20) - 16, 1 << 20, 4 << 20):
+        nblocks = -(-n // 16)
+        alone, beside = f(nr, n, False), f(nr, n, True)
+        assert (alone.bpt, alone.wg, alone.placement) == _ctr_variant(nr, nblocks)
+        whole = 352 << 10 < n < 1 << 20
+        assert (beside.bpt != aes.AES_BPT_COLUMN) == (whole or alone.bpt != aes.AES_BPT_COLUMN), n
+        if not whole:
+            assert beside.bpt == alone.bpt
+        old = aes.aes_tune_get(nr, False, nblocks)
+        try:
+            aes.aes_tune_set(nr, False, nblocks, aes.Variant(aes.AES_BPT_COLUMN, 192, 0))
+            v = f(nr, n, True)
+            assert (v.bpt, v.wg, v.placement) == (aes.AES_BPT_COLUMN, 192, 0)
+        finally:
+            aes.aes_tune_set(nr, False, nblocks, old)
