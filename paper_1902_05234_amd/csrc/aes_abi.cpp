@@ -476,7 +476,7 @@ int check_batch(const aes_work_item* items_dev, size_t n_enc, size_t n_dec, cons
     }
     out->args = BatchArgs{reinterpret_cast<const WorkItem*>(items_dev), (uint32_t)n_enc, (uint32_t)n_dec,
                           key_table_dev, (uint32_t)n_slots, in_base, out_base, (uint64_t)in_blocks,
-                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, few.parts_log2,
+                          (uint64_t)out_blocks, nullptr, (uint32_t)enc_groups, few.grid != 0, few.parts_log2,
                           claims_worth(in_blocks, (uint64_t)n_enc + n_dec)};
     out->bpt = c.bpt;
     out->wg = c.wg;

@@ -9,8 +9,8 @@
 // is walked in parts of items, so that it spreads over all CUs; the serving
 // engine's batches, several at a time on the device, go item by item.
 // (Time per launch, 4 tables, items of 2048 blocks: 30 messages of up to 1 MiB
-// 83 -> 9.5 us, 1000 of up to 4 KiB 43 -> 9.7, 2000 of up to 8 MiB 1160 ->
-// 1115, against items claimed one by one, each by one wave.)
+// 112 -> 8.1 us, 1000 of up to 4 KiB 43 -> 7.4, 2000 of up to 8 MiB 1015 -> 970,
+// against items claimed one by one, each by one wave.)
 //
 // LDS holds the tables of one direction only (4 tables: 128 KiB + 32 KiB of
 // InvS; 2 tables: 64 + 8 KiB; 1 table: 32 + 8 KiB), so the workgroups are
@@ -87,10 +87,55 @@ __device__ __forceinline__ void run_item(const uint4* __restrict__ in, uint4* __
     }
 }
 
+// Item `it` of a list, or part `part` of the 2^lp (kParts) that it is walked in;
+// returns its length.  A bad item is counted once.
+template <bool kDecrypt, int BPT, int PL, bool kParts>
+__device__ __forceinline__ uint32_t walk_item(const WorkItem& it, uint32_t part, uint32_t lp,
+                                              const uint32_t* __restrict__ key_table, uint32_t n_slots,
+                                              const uint4* __restrict__ in_base, uint4* __restrict__ out_base,
+                                              uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
+                                              const uint32_t* lds, const LaneBases<PL, kDecrypt>& lb)
+{
+    const uint64_t in_b = __builtin_amdgcn_readfirstlane((uint32_t)it.in_block) |
+                          ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.in_block >> 32)) << 32);
+    const uint64_t out_b = __builtin_amdgcn_readfirstlane((uint32_t)it.out_block) |
+                           ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.out_block >> 32)) << 32);
+    const uint32_t nb = __builtin_amdgcn_readfirstlane(it.nblocks);
+    const uint32_t slot = __builtin_amdgcn_readfirstlane(it.key_slot);
+    const bool ok = slot < n_slots && nb <= AES_MAX_ITEM_BLOCKS && in_b <= in_blocks && nb <= in_blocks - in_b &&
+                    out_b <= out_blocks && nb <= out_blocks - out_b;
+    const uint32_t* kp = key_table + (uint64_t)(ok ? slot : 0u) * kSlotWords;
+    const int nr = ok ? (int)__builtin_amdgcn_readfirstlane(kp[kSlotNr]) : 0;
+    const uint32_t* kd = kp + (kDecrypt ? 64 : 0);
+    const uint4* src = in_base + in_b;
+    uint4* dst = out_base + out_b;
+    uint32_t n = nb;
+    if constexpr (kParts) {
+        // The part's blocks: an equal share, in wave rows of 64 blocks.  An item
+        // moved within one arena onto part of itself goes whole to its first
+        // part's wave, which reads every block before it writes there.
+        const bool onto_itself = in_base == out_base && in_b != out_b && in_b < out_b + nb && out_b < in_b + nb;
+        const uint32_t share = onto_itself ? nb : ((nb + (64u << lp) - 1u) >> (6u + lp)) << 6;
+        const uint32_t from = part * share;  // below 2^30 for an item that is ok
+        n = from < nb ? (nb - from < share ? nb - from : share) : 0u;
+        src += from;
+        dst += from;
+    }
+    switch (nr) {
+    case 10: run_item<10, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
+    case 12: run_item<12, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
+    case 14: run_item<14, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
+    default:
+        if ((threadIdx.x & 63u) == 0 && part == 0)
+            atomicAdd(&counters[3], 1u);
+        break;
+    }
+    return nb;
+}
+
 template <bool kDecrypt, int BPT, int PL>
-__device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32_t first_item, uint32_t lp,
-                                      const Claims& claims, uint32_t first_claim, uint32_t claim_step,
-                                      uint32_t left, uint32_t waves, uint32_t worth,
+__device__ __forceinline__ void drain(const WorkItem* __restrict__ items, const ListClaims& claims,
+                                      uint32_t first_claim, uint32_t claim_step, uint32_t left, uint32_t worth,
                                       const uint32_t* __restrict__ key_table, uint32_t n_slots,
                                       const uint4* __restrict__ in_base, uint4* __restrict__ out_base,
                                       uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
@@ -108,7 +153,7 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
             dealt += claim_step;
         } else if (claims.dealt < claims.n) {
             if (run == 0) {
-                run = taken = claims_at_once(left, waves, taken, longest, worth);
+                run = taken = claims_at_once(left, claims.per_wave, taken, longest, worth);
                 longest = 0;
                 if (lane == 0)
                     next = claims.dealt + atomicAdd(counter, run);
@@ -120,61 +165,31 @@ __device__ __forceinline__ void drain(const WorkItem* __restrict__ items, uint32
         }
         if (idx >= claims.n)
             break;
-        const uint32_t part = idx & ((1u << lp) - 1u);
-        const WorkItem it = items[first_item + (idx >> lp)];
-        const uint64_t in_b = __builtin_amdgcn_readfirstlane((uint32_t)it.in_block) |
-                              ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.in_block >> 32)) << 32);
-        const uint64_t out_b = __builtin_amdgcn_readfirstlane((uint32_t)it.out_block) |
-                               ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(it.out_block >> 32)) << 32);
-        const uint32_t nb = __builtin_amdgcn_readfirstlane(it.nblocks);
-        const uint32_t slot = __builtin_amdgcn_readfirstlane(it.key_slot);
-        longest = max(longest, nb);
-        const bool ok = slot < n_slots && nb <= AES_MAX_ITEM_BLOCKS && in_b <= in_blocks && nb <= in_blocks - in_b &&
-                        out_b <= out_blocks && nb <= out_blocks - out_b;
-        const uint32_t* kp = key_table + (uint64_t)(ok ? slot : 0u) * kSlotWords;
-        const int nr = ok ? (int)__builtin_amdgcn_readfirstlane(kp[kSlotNr]) : 0;
-        const uint32_t* kd = kp + (kDecrypt ? 64 : 0);
-        // The part's blocks: an equal share, in wave rows of 64 blocks.  An item
-        // moved within one arena onto part of itself goes whole to its first
-        // part's wave, which reads every block before it writes there.
-        const bool onto_itself = in_base == out_base && in_b != out_b && in_b < out_b + nb && out_b < in_b + nb;
-        const uint32_t share = lp == 0 || onto_itself ? nb : ((nb + (64u << lp) - 1u) >> (6u + lp)) << 6;
-        const uint32_t from = part * share;  // below 2^30 for an item that is ok
-        const uint32_t n = from < nb ? (nb - from < share ? nb - from : share) : 0u;
-        const uint4* src = in_base + in_b + from;
-        uint4* dst = out_base + out_b + from;
-        switch (nr) {
-        case 10: run_item<10, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
-        case 12: run_item<12, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
-        case 14: run_item<14, kDecrypt, BPT, PL>(src, dst, n, lds, lb, kd); break;
-        default:
-            if (lane == 0 && part == 0)
-                atomicAdd(&counters[3], 1u);
-            break;
-        }
+        longest = max(longest, walk_item<kDecrypt, BPT, PL, false>(items[idx], 0u, 0u, key_table, n_slots, in_base,
+                                                                   out_base, in_blocks, out_blocks, counters, lds, lb));
     }
 }
 
 // The 2- and 1-table kernels are built for 8 waves per SIMD (at most 64
 // VGPRs), so two 1024-thread workgroups share a CU, as in the plain kernel.
+#define AESGPU_BATCH_KERNEL(PL) \
+    __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu((PL) == kPlace4 ? 4 : 8))) void
+
 template <int BPT, int PL>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPlace4 ? 4 : 8))) void batch_kernel(const WorkItem* __restrict__ items, uint32_t n_enc,
-                                                     uint32_t n_dec, const uint32_t* __restrict__ key_table,
-                                                     uint32_t n_slots, const uint4* __restrict__ in_base,
-                                                     uint4* __restrict__ out_base, uint64_t in_blocks,
-                                                     uint64_t out_blocks, uint32_t* counters, uint32_t enc_groups,
-                                                     uint32_t lp, uint32_t worth, uint32_t* done_word, uint32_t done_seq)
+AESGPU_BATCH_KERNEL(PL)
+batch_kernel(const WorkItem* __restrict__ items, ListClaims enc_claims, ListClaims dec_claims,
+             const uint32_t* __restrict__ key_table, uint32_t n_slots, const uint4* __restrict__ in_base,
+             uint4* __restrict__ out_base, uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
+             uint32_t enc_groups, uint32_t worth, uint32_t* done_word, uint32_t done_seq)
 {
     __shared__ __align__(16) uint32_t lds[Layout<PL, true>::words];  // the larger of the two directions
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), per_group = blockDim.x >> 6;
-    const Claims enc_claims = claims_of(n_enc, lp, enc_groups * per_group, worth);
-    const Claims dec_claims = claims_of(n_dec, lp, (gridDim.x - enc_groups) * per_group, worth);
     bool dec = blockIdx.x >= enc_groups;
     // the wave's place among those that start on its list, and their number
     const uint32_t place = (blockIdx.x - (dec ? enc_groups : 0u)) * per_group + wave;
     const uint32_t step = (dec ? gridDim.x - enc_groups : enc_groups) * per_group;
     for (int pass = 0; pass < 2; ++pass, dec = !dec) {
-        const Claims claims = dec ? dec_claims : enc_claims;
+        const ListClaims claims = dec ? dec_claims : enc_claims;
         uint32_t left = claims.n - claims.dealt;
         if (claims.n == 0)
             continue;  // uniform across the grid: no tables to load, no barrier to meet
@@ -194,19 +209,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPla
             left -= claimed;
         }
         const uint32_t first_claim = pass == 0 ? place : claims.dealt;
-        const uint32_t own = (dec ? gridDim.x - enc_groups : enc_groups) * per_group;
-        const uint32_t waves = claim_waves(own, gridDim.x * per_group);
         if (dec)
             fill_tables<PL, true>(lds, &c_tables);
         else
             fill_tables<PL, false>(lds, &c_tables);
         __syncthreads();
         if (dec)
-            drain<true, BPT, PL>(items, n_enc, lp, claims, first_claim, step, left, waves, worth, key_table, n_slots,
+            drain<true, BPT, PL>(items + enc_claims.n, claims, first_claim, step, left, worth, key_table, n_slots,
                                  in_base, out_base, in_blocks, out_blocks, counters, lds);
         else
-            drain<false, BPT, PL>(items, 0, lp, claims, first_claim, step, left, waves, worth, key_table, n_slots,
-                                  in_base, out_base, in_blocks, out_blocks, counters, lds);
+            drain<false, BPT, PL>(items, claims, first_claim, step, left, worth, key_table, n_slots, in_base, out_base,
+                                  in_blocks, out_blocks, counters, lds);
         __syncthreads();  // every wave is done with these tables before LDS is refilled
     }
     if (threadIdx.x == 0) {
@@ -225,6 +238,37 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(PL == kPla
                 __hip_atomic_store(done_word, done_seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
+    }
+}
+
+// Lists that leave every wave one claim at most (short_list): no counters, no
+// other direction, and so nothing to reset.  A kernel of its own because such a
+// launch takes little longer than its code takes to arrive: 1000 messages of up
+// to 4 KiB 9.9 us in the kernel above with parts, 7.4 so.
+template <int BPT, int PL>
+AESGPU_BATCH_KERNEL(PL)
+batch_short_kernel(const WorkItem* __restrict__ items, uint32_t n_enc, uint32_t n_dec,
+                   const uint32_t* __restrict__ key_table, uint32_t n_slots, const uint4* __restrict__ in_base,
+                   uint4* __restrict__ out_base, uint64_t in_blocks, uint64_t out_blocks, uint32_t* counters,
+                   uint32_t enc_groups, uint32_t lp)
+{
+    __shared__ __align__(16) uint32_t lds[Layout<PL, true>::words];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), per_group = blockDim.x >> 6;
+    const bool dec = blockIdx.x >= enc_groups;
+    const uint32_t claim = (blockIdx.x - (dec ? enc_groups : 0u)) * per_group + wave;
+    const uint32_t part = claim & ((1u << lp) - 1u), item = claim >> lp;
+    if (dec) {
+        fill_tables<PL, true>(lds, &c_tables);
+        __syncthreads();
+        if (item < n_dec)
+            walk_item<true, BPT, PL, true>(items[n_enc + item], part, lp, key_table, n_slots, in_base, out_base,
+                                           in_blocks, out_blocks, counters, lds, LaneBases<PL, true>(threadIdx.x));
+    } else {
+        fill_tables<PL, false>(lds, &c_tables);
+        __syncthreads();
+        if (item < n_enc)
+            walk_item<false, BPT, PL, true>(items[item], part, lp, key_table, n_slots, in_base, out_base, in_blocks,
+                                            out_blocks, counters, lds, LaneBases<PL, false>(threadIdx.x));
     }
 }
 
@@ -310,11 +354,23 @@ namespace {
 hipError_t launch_batch_impl(const BatchArgs& a, int bpt, int placement, int grid, int wg, uint32_t* done_word,
                              uint32_t seq, hipStream_t stream)
 {
+    const uint64_t per_group = (uint64_t)wg / 64u;
+    const uint32_t all = (uint32_t)std::min<uint64_t>(UINT32_MAX, (uint64_t)grid * per_group);
+    const uint32_t enc = (uint32_t)std::min<uint64_t>(all, a.enc_groups * per_group);
+    const ListClaims enc_claims = list_claims(a.n_enc, enc, all, a.claims_worth);
+    const ListClaims dec_claims = list_claims(a.n_dec, all - enc, all, a.claims_worth);
+    const bool one_each = a.one_claim_each && done_word == nullptr;
 #define AESGPU_BATCH_LAUNCH(B, P)                                                                                  \
-    hipLaunchKernelGGL((batch_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, a.n_enc, a.n_dec,           \
-                       a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base), static_cast<uint4*>(a.out_base), \
-                       a.in_blocks, a.out_blocks, a.counters, a.enc_groups, a.parts_log2, a.claims_worth, \
-                       done_word, seq)
+    if (one_each)                                                                                                  \
+        hipLaunchKernelGGL((batch_short_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, a.n_enc, a.n_dec, \
+                           a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base),                           \
+                           static_cast<uint4*>(a.out_base), a.in_blocks, a.out_blocks, a.counters, a.enc_groups,   \
+                           a.parts_log2);                                                                          \
+    else                                                                                                           \
+        hipLaunchKernelGGL((batch_kernel<B, P>), dim3(grid), dim3(wg), 0, stream, a.items, enc_claims, dec_claims, \
+                           a.key_table, a.n_slots, static_cast<const uint4*>(a.in_base),                           \
+                           static_cast<uint4*>(a.out_base), a.in_blocks, a.out_blocks, a.counters, a.enc_groups,   \
+                           a.claims_worth, done_word, seq)
 #define AESGPU_BATCH_PLACEMENT(P)                   \
     switch (bpt) {                                  \
     case 1: AESGPU_BATCH_LAUNCH(1, P); break;       \
@@ -330,6 +386,7 @@ hipError_t launch_batch_impl(const BatchArgs& a, int bpt, int placement, int gri
     }
 #undef AESGPU_BATCH_PLACEMENT
 #undef AESGPU_BATCH_LAUNCH
+#undef AESGPU_BATCH_KERNEL
     return hipGetLastError();
 }
 

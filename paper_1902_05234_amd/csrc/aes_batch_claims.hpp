@@ -21,26 +21,25 @@ constexpr uint32_t claims_worth(uint64_t blocks, uint64_t n)
     return 1u + static_cast<uint32_t>(1200u / (mean != 0 ? mean : 1u));
 }
 
-// The claims of one list: 2^lp parts of each item, of which the first `dealt`
-// go to the `waves` waves that start on the list, in turn, and the rest to
-// whichever wave asks, through the list's counter.  An update of the counter
-// takes about 14 ns in which no other is served: 1000 items of one unit on 1008
+// The claims of one list, an item each, of which the first `dealt` go to the
+// `waves` waves that start on the list, in turn, and the rest to whichever
+// wave asks, through the list's counter.  An update of the counter takes
+// about 14 ns in which no other is served: 1000 items of one unit on 1008
 // waves took 43 us, the time of their 3000 updates.  So a list that one claim
 // per wave covers is dealt whole.  Of a longer one every wave gets one claim,
 // as it would at once from the counter, and more only up to five eighths of
-// its share, 8, and what is worth an update: dealt claims stay with their wave,
-// and dealt waves drift apart over the arenas.  (us; one by one, the five
-// eighths rounded up and of any length, and so: 20,000 messages of up to 8 MiB
-// in items of 2048 blocks 9957, 10431, 9846; of up to 4 KiB 328, 166, 149;
-// 10,000 items of 4 blocks, one in a hundred of 20,000, 615, 796, 573; 8192
-// items of 2048 blocks beside as many of one block 370, 350, 287.)
+// its share, 8, and what is worth an update: dealt claims stay with their
+// wave, and dealt waves drift apart over the arenas.  (us; one by one, the
+// five eighths rounded up and of any length, and so: 20,000 messages of up to
+// 8 MiB in items of 2048 blocks 9957, 10431, 9846; of up to 4 KiB 328, 166,
+// 149; 10,000 items of 4 blocks, one in a hundred of 20,000, 615, 796, 573;
+// 8192 items of 2048 blocks beside as many of one block 370, 350, 287.)
 struct Claims {
     uint32_t n, dealt;
 };
 
-constexpr Claims claims_of(uint32_t n_items, uint32_t lp, uint32_t waves, uint32_t worth)
+constexpr Claims claims_of(uint32_t n, uint32_t waves, uint32_t worth)
 {
-    const uint32_t n = n_items << lp;
     if (n <= waves || waves == 0)
         return Claims{n, waves == 0 ? 0u : n};
     const uint32_t share = n / waves, part = share < 13u ? share * 5u / 8u : 8u;
@@ -56,14 +55,27 @@ constexpr Claims claims_of(uint32_t n_items, uint32_t lp, uint32_t waves, uint32
 // now.)
 constexpr uint32_t claim_waves(uint32_t own, uint32_t all) { return own > all / 2u ? own : (all + 1u) / 2u; }
 
-// Claims taken with one update of the counter when `left` are left for `waves`
-// waves: a sixteenth of a wave's share and one, and twice as many as the last
+// What a launch hands its kernel for one list: the claims, and the claims that
+// each of claim_waves is to have, as a factor over 2^32.
+struct ListClaims {
+    uint32_t n, dealt, per_wave;
+};
+
+constexpr ListClaims list_claims(uint32_t n, uint32_t own, uint32_t all, uint32_t worth)
+{
+    const Claims c = claims_of(n, own, worth);
+    return ListClaims{c.n, c.dealt, UINT32_MAX / claim_waves(own, all)};
+}
+
+// Claims taken with one update of the counter when `left` are left, per_wave as
+// above: a sixteenth of a wave's share and one, and twice as many as the last
 // time, up to two fifths of the share, where none of those was over 512 blocks
 // (100,000 messages of up to 1 KiB 1234 us one by one, 299 so; of up to 8 KiB
 // 1236 -> 327; half the share: 282 and 310, but its last runs end unevenly).
-constexpr uint32_t claims_at_once(uint32_t left, uint32_t waves, uint32_t taken, uint32_t longest, uint32_t worth)
+constexpr uint32_t claims_at_once(uint32_t left, uint32_t per_wave, uint32_t taken, uint32_t longest, uint32_t worth)
 {
-    const uint32_t few = 1u + left / 16u / waves, most = 1u + (left / waves + 1u) * 2u / 5u;
+    const uint32_t share = static_cast<uint32_t>((uint64_t{left} * per_wave) >> 32);
+    const uint32_t few = 1u + share / 16u, most = 1u + (share + 1u) * 2u / 5u;
     const uint32_t more = longest > 512u ? few : 2u * taken < most ? 2u * taken : most;
     const uint32_t n = few > more ? few : more;
     return n < worth ? n : worth;

@@ -88,10 +88,11 @@ struct BatchArgs {
     uint64_t out_blocks;
     uint32_t* counters;    // [0] next enc item, [1] next dec item, [2] finished groups, [3] rejected items
     uint32_t enc_groups;   // workgroups that start on the encryption list
-    // Every item is claimed in 2^parts_log2 parts of whole wave rows (64
-    // blocks), so that several waves share one; 0: an item by one wave, as in
-    // the serving engine's launches.  Where it is not 0 there are no more parts
-    // of all items than resident waves (short_list in aes_batch_claims.hpp).
+    // A list that leaves every wave of the grid one claim at most, an item being
+    // 2^parts_log2 claims of whole wave rows (64 blocks) each, so that several
+    // waves share one (short_list in aes_batch_claims.hpp).  The serving
+    // engine's launches go item by item.
+    bool one_claim_each = false;
     uint32_t parts_log2 = 0;
     uint32_t claims_worth = 1;  // most claims taken with one update of a counter (aes_batch_claims.hpp)
 };

@@ -252,7 +252,7 @@ bool launch(aes_server* s, Slot& sl, std::vector<Req*>& batch)
         const void* items = direct ? static_cast<const void*>(sl.staging) : static_cast<const void*>(sl.items_dev);
         BatchArgs a{static_cast<const WorkItem*>(items), (uint32_t)ne, (uint32_t)nd, s->key_table,
                     (uint32_t)s->n_slots, s->in_pool, s->out_arena, (uint64_t)s->in_blocks, (uint64_t)s->out_blocks,
-                    sl.counters_dev, (uint32_t)enc_groups, 0u, claims_worth(tot_b, n)};
+                    sl.counters_dev, (uint32_t)enc_groups, false, 0u, claims_worth(tot_b, n)};
         // with completion words the kernel's last workgroup writes the word
         e = s->use_done_word
                 ? launch_batch_signal(a, s->cfg.bpt, s->cfg.placement, grid, s->cfg.wg, sl.done_word, sl.seq + 1,

@@ -15,15 +15,15 @@ from paper_1902_05234_amd import inputs
 CSRC = os.path.join(os.path.dirname(__file__), "..", "paper_1902_05234_amd", "csrc")
 WRAPPER = """
 #include "aes_batch_claims.hpp"
-extern "C" uint32_t dealt(uint32_t n, uint32_t lp, uint32_t waves, uint32_t worth)
+extern "C" uint32_t dealt(uint32_t n, uint32_t waves, uint32_t worth)
 {
-    return aesgpu::claims_of(n, lp, waves, worth).dealt;
+    return aesgpu::claims_of(n, waves, worth).dealt;
 }
 extern "C" uint32_t claim_waves(uint32_t own, uint32_t all) { return aesgpu::claim_waves(own, all); }
 extern "C" uint32_t claims_worth(uint64_t blocks, uint64_t n) { return aesgpu::claims_worth(blocks, n); }
 extern "C" uint32_t at_once(uint32_t left, uint32_t waves, uint32_t taken, uint32_t longest, uint32_t worth)
 {
-    return aesgpu::claims_at_once(left, waves, taken, longest, worth);
+    return aesgpu::claims_at_once(left, aesgpu::list_claims(0, waves, waves, 1).per_wave, taken, longest, worth);
 }
 extern "C" void short_list(uint64_t n_enc, uint64_t n_dec, uint32_t per_group, uint64_t max_grid, uint64_t resident,
                            uint32_t* out)
@@ -54,7 +54,7 @@ def play(lists, groups, per_group, rules=None):
     workgroups is done with both lists; rules None: one claim at a time."""
     total = sum(groups) * per_group
     worth = rules.claims_worth(int(sum(map(np.sum, lists))), sum(map(len, lists))) if rules else 1
-    dealt = [rules.dealt(len(x), 0, g * per_group, worth) if rules else 0 for x, g in zip(lists, groups)]
+    dealt = [rules.dealt(len(x), g * per_group, worth) if rules else 0 for x, g in zip(lists, groups)]
     counter, times, done = [0, 0], [], [0, 0]
     heap = []  # (time, workgroup, wave) of waves that look for an item; state beside it
     state = {}
