@@ -179,7 +179,8 @@ int aes_cbc_decrypt_variant(const uint32_t *rk, int nr, const uint8_t *iv, const
  * under one key, in one launch.  Within a message each block needs the
  * previous ciphertext block, so a message cannot be split (Table 1 marks
  * CBC encryption unsuitable for parallel work); the parallelism is across
- * messages: each message is one chain, walked by one GPU lane.
+ * messages: each message is one chain, walked by one GPU lane in long lists
+ * and by four or sixteen together in shorter ones.
  *   rk:        host pointer to the ENCRYPTION schedule (rk_enc), copied.
  *   nr:        10, 12 or 14.
  *   msgs_dev:  device array of nmsgs aes_cbc_msg, 16-byte aligned.  Message

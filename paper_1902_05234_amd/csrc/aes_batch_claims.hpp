@@ -31,9 +31,9 @@ constexpr uint32_t claims_worth(uint64_t blocks, uint64_t n)
 // its share, 8, and what is worth an update: dealt claims stay with their
 // wave, and dealt waves drift apart over the arenas.  (us; one by one, the
 // five eighths rounded up and of any length, and so: 20,000 messages of up to
-// 8 MiB in items of 2048 blocks 9957, 10431, 9846; of up to 4 KiB 328, 166,
-// 149; 10,000 items of 4 blocks, one in a hundred of 20,000, 615, 796, 573;
-// 8192 items of 2048 blocks beside as many of one block 370, 350, 287.)
+// 8 MiB in items of 2048 blocks 9685, 10181, 9556; of up to 4 KiB 327, 165,
+// 146; 10,000 items of 4 blocks, one in a hundred of 20,000, 612, 787, 568;
+// 8192 items of 2048 blocks beside as many of one block 371, 349, 309.)
 struct Claims {
     uint32_t n, dealt;
 };
@@ -51,7 +51,7 @@ constexpr Claims claims_of(uint32_t n, uint32_t waves, uint32_t worth)
 // of the launch where these are fewer, because the others come over once
 // their own list is dry.  (With the starting waves of a wave's own list for
 // both, 10 encryption and 50,000 decryption items of 256 blocks left 17,360
-// claims to sixteen helping waves in runs of 68: 672 us one by one, 950 so, 222
+// claims to sixteen helping waves in runs of 68: 679 us one by one, 945 so, 233
 // now.)
 constexpr uint32_t claim_waves(uint32_t own, uint32_t all) { return own > all / 2u ? own : (all + 1u) / 2u; }
 
@@ -70,8 +70,8 @@ constexpr ListClaims list_claims(uint32_t n, uint32_t own, uint32_t all, uint32_
 // Claims taken with one update of the counter when `left` are left, per_wave as
 // above: a sixteenth of a wave's share and one, and twice as many as the last
 // time, up to two fifths of the share, where none of those was over 512 blocks
-// (100,000 messages of up to 1 KiB 1234 us one by one, 299 so; of up to 8 KiB
-// 1236 -> 327; half the share: 282 and 310, but its last runs end unevenly).
+// (100,000 messages of up to 1 KiB 1238 us one by one, 300 so; of up to 8 KiB
+// 1247 -> 330; half the share: 282 and 310, but its last runs end unevenly).
 constexpr uint32_t claims_at_once(uint32_t left, uint32_t per_wave, uint32_t taken, uint32_t longest, uint32_t worth)
 {
     const uint32_t share = static_cast<uint32_t>((uint64_t{left} * per_wave) >> 32);

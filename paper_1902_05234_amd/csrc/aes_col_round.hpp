@@ -4,9 +4,10 @@
 // so a lane issues four lookups per round instead of sixteen.  The round is
 // eq 26: output column j needs byte t of W_{j+t} (W_{j-t} for decryption),
 // and DPP quad permutations (one VALU move each) bring those three neighbour
-// words to the lane.  Used by the one-column-per-lane ECB kernel and by the
-// four-lanes-per-message CBC encryption kernel.  A quad is always wholly
-// active or wholly idle, so the permutations read only active lanes.
+// words to the lane.  Used by the one-column-per-lane kernels of ECB, CTR and
+// CBC decryption and by the four-lanes-per-message CBC encryption kernel.  A
+// quad is always wholly active or wholly idle, so the permutations read only
+// active lanes.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
